@@ -68,6 +68,11 @@ enum KernelKind : int32_t {
     K_TT_PREP = 38,         // its convolution's A operands in load order (TtDesc)
     K_WGCONV = 39,          // K_CREDW's partials on fp32 MFMA tiles (CredDesc)
     K_GPAIR = 40,           // both gradients of a channel-mixing step from one read of dC (GpairDesc)
+    K_DCONV = 41,           // dense 2-D convolution with a packed kernel (DConvDesc, desc_dense.h)
+    K_DWGRAD = 42,          // partials of its kernel's gradient (DWgradDesc)
+    K_RCP_MERGE = 43,       // merged, packed kernel of a reshaped-CP layer (DRcpDesc)
+    K_RCP_DFWD = 45,        // reshaped-CP forward merging its kernel on chip (RcpDfwdDesc)
+    K_RCP_FGRAD = 44,       // its factor gradients' partials from the kernel's gradient (DRcpDesc)
 };
 
 // Launch kind = variant | element-type bits (1 = bfloat16, 0 = float32).

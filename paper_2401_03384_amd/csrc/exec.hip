@@ -55,10 +55,11 @@ hipError_t raw_launch(const Launch& ln, const Ptrs& P, hipStream_t s) {
             const void* ops[4] = {a, b, resolve(ln.extra[0], P), resolve(ln.extra[1], P)};
             return launch_tt_fwd(ln, ops, c, s);
         }
-        case K_RCP_FWD: {
+        case K_RCP_FWD:
+        case K_RCP_DFWD: {
             const void* ops[5] = {a, b, resolve(ln.extra[0], P), resolve(ln.extra[1], P),
                                   resolve(ln.extra[2], P)};
-            return launch_rcp_fwd(ln, ops, c, s);
+            return variant == K_RCP_DFWD ? launch_rcp_dfwd(ln, ops, c, s) : launch_rcp_fwd(ln, ops, c, s);
         }
         case K_RCP_BWD: {
             const void* ops[12] = {a, b};
@@ -69,6 +70,18 @@ hipError_t raw_launch(const Launch& ln, const Ptrs& P, hipStream_t s) {
             const void* ops[5];
             for (int i = 0; i < 5; i++) ops[i] = resolve(ln.extra[i], P);
             return launch_rcp_prep(ln, ops, s);
+        }
+        case K_DCONV: return launch_dconv(ln, a, b, c, s);
+        case K_DWGRAD: return launch_dwgrad(ln, a, b, d, s);
+        case K_RCP_MERGE: {
+            const void* ops[5];
+            for (int i = 0; i < 5; i++) ops[i] = resolve(ln.extra[i], P);
+            return launch_rcp_merge(ln, ops, s);
+        }
+        case K_RCP_FGRAD: {
+            const void* ops[9];
+            for (int i = 0; i < 9; i++) ops[i] = resolve(ln.extra[i], P);
+            return launch_rcp_fgrad(ln, ops, s);
         }
         case K_CP_BWD: {
             const void* ops[11] = {a, b, c};

@@ -21,28 +21,40 @@ namespace {
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
-}  // namespace
+// A plan that applies the four factors of a reshaped-CP layer one at a time.
+struct RcpShape {
+    int X, f[4];                  // operands: the feature, W1, W2, W3, W0
+    int64_t S[3], T[3], K, B, H, W, R;
+};
 
-bool fuse_rcp_forward(const ce_plan& p, Launch& out) {
+// any_order: whatever the planned order (operands found by their labels).
+bool match_rcp(const ce_plan& p, RcpShape& o, bool any_order = false) {
     const ce_expr& E = p.e;
-    if (p.dtype != CE_BF16 || E.n != 5 || p.steps.size() != 4) return false;
-    const int X = E.feature_operand;
+    if (E.n != 5 || p.steps.size() != 4) return false;
+    const int X = o.X = E.feature_operand;
+    int* f = o.f;
+    int64_t *S = o.S, *T = o.T;
     if (X != 0) return false;
+    const std::vector<int>& xl = E.ops[X];
+    if (xl.size() != 6 || E.out.size() != 6) return false;
     // the chain: ((((X, F1), F2), F3), F0)
-    int f[4];
+    for (int s = 0; s < 4; s++) f[s] = -1;
     for (int s = 0; s < 4; s++) {
+        if (any_order) {
+            for (int i = 1; i < 5; i++)
+                if (E.ops[i].size() == 3 && E.ops[i][2] == xl[s < 3 ? 1 + s : 5]) f[s] = i;
+            if (f[s] < 0) return false;
+            continue;
+        }
         const Step& st = p.steps[s];
         if (st.a != (s == 0 ? X : p.steps[s - 1].c) || st.b >= E.n || st.b == X) return false;
         f[s] = st.b;
     }
-    const std::vector<int>& xl = E.ops[X];
-    if (xl.size() != 6 || E.out.size() != 6) return false;
     const int lb = xl[0], lh = xl[4], lw = xl[5];
     if (!E.is_conv(lh) || !E.is_conv(lw) || E.is_conv(lb) || E.feature_of(lh) != X || E.feature_of(lw) != X)
         return false;
     // mode factors [r][t_i][s_i] with s_i the (i+1)-th label of X, in step order
     int lr = -1, lt[3];
-    int64_t S[3], T[3];
     for (int i = 0; i < 3; i++) {
         const std::vector<int>& l = E.ops[f[i]];
         if (l.size() != 3 || l[2] != xl[1 + i] || E.is_conv(l[0]) || E.is_conv(l[1])) return false;
@@ -58,8 +70,8 @@ bool fuse_rcp_forward(const ce_plan& p, Launch& out) {
     // spatial factor [r][h][w]
     const std::vector<int>& l0 = E.ops[f[3]];
     if (l0.size() != 3 || l0[0] != lr || l0[1] != lh || l0[2] != lw) return false;
-    const int64_t K = E.dims[f[3]][1];
-    if (E.dims[f[3]][2] != K || K % 2 == 0) return false;
+    const int64_t K = o.K = E.dims[f[3]][1];
+    if (E.dims[f[3]][2] != K) return false;
     // output [b][t1][t2][t3][h][w]
     const std::vector<int>& ol = E.out;
     if (ol[0] != lb || ol[1] != lt[0] || ol[2] != lt[1] || ol[3] != lt[2] || ol[4] != lh || ol[5] != lw)
@@ -69,9 +81,22 @@ bool fuse_rcp_forward(const ce_plan& p, Launch& out) {
         if (i != X)
             for (int l : E.ops[i])
                 if (l == lb) return false;
-    const int64_t B = E.dims[X][0], H = E.dims[X][4], W = E.dims[X][5];
-    const int64_t R = E.dims[f[0]][0];
-    if (B < 1 || H < K || W < K || R < 2 || R % 2) return false;
+    o.B = E.dims[X][0];
+    o.H = E.dims[X][4];
+    o.W = E.dims[X][5];
+    o.R = E.dims[f[0]][0];
+    return o.B >= 1 && o.H >= K && o.W >= K;
+}
+
+}  // namespace
+
+bool fuse_rcp_forward(const ce_plan& p, Launch& out) {
+    RcpShape q;
+    if (p.dtype != CE_BF16 || !match_rcp(p, q)) return false;
+    const int X = q.X;
+    const int *f = q.f;
+    const int64_t *S = q.S, *T = q.T, B = q.B, H = q.H, W = q.W, R = q.R, K = q.K;
+    if (K % 2 == 0 || R < 2 || R % 2) return false;
     if (B * S[0] * S[1] * S[2] * H * W >= (1ll << 31) || B * T[0] * T[1] * T[2] * H * W >= (1ll << 31))
         return false;
     for (int c = 0; c < kNumRcpCfgs; c++) {
@@ -321,6 +346,297 @@ bool fuse_rcp_backward(const Launch& f, const ce_plan& p, ScratchAlloc& scratch,
         return true;
     }
     return false;
+}
+
+}  // namespace ce
+
+// ---- the dense-kernel form ---------------------------------------------------
+namespace ce {
+
+namespace {
+
+// Sizes the merge and gradient kernels take: 64 x 64 tiles of
+// (s1 s2) x (t3 s3), taps in dwgrad's groups.
+bool dense_rcp_shape(const ce_plan& p, RcpShape& q) {
+    if (!match_rcp(p, q, true)) return false;
+    const int64_t KT = q.K * q.K, HW = q.H * q.W;
+    if (q.S[0] * q.S[1] > 64 || q.T[2] * q.S[2] > 64 || (q.K != 3 && q.K != 5) || q.R > 4096) return false;
+    const int64_t S = q.S[0] * q.S[1] * q.S[2], T = q.T[0] * q.T[1] * q.T[2];
+    return S <= 4096 && T <= 4096 && HW <= (1 << 20) && q.B <= (1 << 24);
+}
+
+DTile same_tile(const RcpShape& q, bool reversed) {
+    DTile t;
+    std::memset(&t, 0, sizeof(t));
+    t.B = (int32_t)q.B;
+    t.H = t.OH = (int32_t)q.H;
+    t.W = t.OW = (int32_t)q.W;
+    t.KH = t.KW = (int32_t)q.K;
+    const int32_t c = (int32_t)((q.K - 1) / 2);
+    // forward: input position p + i - c; input gradient: p - i + c
+    t.zh0 = t.zw0 = reversed ? c : -c;
+    t.zhs = t.zws = reversed ? -1 : 1;
+    t.sth = t.stw = 1;
+    return t;
+}
+
+DRcpDesc rcp_desc(const RcpShape& q) {
+    DRcpDesc d;
+    std::memset(&d, 0, sizeof(d));
+    d.R = (int32_t)q.R;
+    d.T1 = (int32_t)q.T[0]; d.T2 = (int32_t)q.T[1]; d.T3 = (int32_t)q.T[2];
+    d.S1 = (int32_t)q.S[0]; d.S2 = (int32_t)q.S[1]; d.S3 = (int32_t)q.S[2];
+    d.KT = (int32_t)(q.K * q.K);
+    d.nrc = (int32_t)((q.R + 63) / 64);
+    return d;
+}
+
+// taps a block takes: enough blocks for two a CU where the taps allow it
+void tap_groups(DRcpDesc& d, int64_t per_tap) {
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(d.KT, 512 / std::max<int64_t>(1, per_tap)));
+    d.jper = (int32_t)((d.KT + want - 1) / want);
+    d.NJ = (d.KT + d.jper - 1) / d.jper;
+}
+
+// merge + convolution launches: rows T of W (forward, x = the features) or
+// rows S (input gradient, x = the output gradient)
+bool dense_rcp_conv(const RcpShape& q, bool bf16, bool grad, ScratchAlloc& scratch, std::vector<Launch>& out) {
+    const int64_t S = q.S[0] * q.S[1] * q.S[2], T = q.T[0] * q.T[1] * q.T[2], HW = q.H * q.W;
+    DConvDesc d;
+    std::memset(&d, 0, sizeof(d));
+    d.t = same_tile(q, grad);
+    d.C = (int32_t)(grad ? T : S);
+    d.M = (int32_t)(grad ? S : T);
+    d.x_sb = d.C * HW;
+    d.x_sc = d.y_sm = HW;
+    d.y_sb = d.M * HW;
+    d.y_sh = q.W;
+    d.y_sw = 1;
+    Launch lc;
+    if (!plan_dconv(d, bf16, lc)) return false;
+    DRcpDesc m = rcp_desc(q);
+    m.transposed = grad;
+    m.nch = d.nch;
+    tap_groups(m, (int64_t)m.T1 * m.T2);
+    m.blocks = (int64_t)m.T1 * m.T2 * m.NJ;
+    const uint32_t need = grad ? 1u << q.X : 0u;
+    const int64_t packed = (int64_t)((d.M + 31) / 32) * d.nch * m.KT * 2048;
+    const BufRef A = scratch.alloc((size_t)packed);
+    auto in = [](int i) {
+        BufRef b;
+        b.kind = BUF_IN;
+        b.index = i;
+        return b;
+    };
+    const int bits = bf16 ? (1 << kBitIn) | (1 << kBitOut) : 0;
+    Launch lm;
+    lm.kind = K_RCP_MERGE | bits;
+    lm.extra = {in(q.f[0]), in(q.f[1]), in(q.f[2]), in(q.f[3]), A};
+    lm.grid[0] = (uint32_t)m.blocks;
+    lm.block[0] = 256;
+    lm.lds = (uint32_t)(4 * (128 * 68 + 64 * m.KT));
+    lm.desc.resize(sizeof(m));
+    std::memcpy(lm.desc.data(), &m, sizeof(m));
+    lm.need = need;
+    lm.what = "merged kernel of the reshaped-CP layer";
+    lm.kname = bf16 ? "rcp_merge<unsigned short>" : "rcp_merge<float>";
+    lm.alg_bytes = (double)packed;
+    lm.alg_flops = 2.0 * (double)S * T * m.KT * q.R;
+    out.push_back(lm);
+    lc.a = in(q.X);
+    lc.c.kind = BUF_OUT;
+    if (grad) {
+        lc.a.kind = BUF_DOUT;
+        lc.c.kind = BUF_DIN;
+        lc.c.index = q.X;
+    }
+    lc.b = A;
+    lc.need = need;
+    lc.what = grad ? "dX: dY convolved with the merged kernel" : "X convolved with the merged kernel";
+    out.push_back(lc);
+    return true;
+}
+
+}  // namespace
+
+bool dense_rcp_onelaunch(const ce_plan& p, Launch& f) {
+    RcpShape q;
+    if ((f.kind & 0xff) != K_RCP_FWD || p.dtype != CE_BF16 || !dense_rcp_shape(p, q)) return false;
+    const int64_t S1 = q.S[0], T23 = q.T[1] * q.T[2], S23 = q.S[1] * q.S[2];
+    const bool k3 = q.K == 3 && S1 == 8 && T23 == 64, k5 = q.K == 5 && S1 == 4 && T23 == 32;
+    if ((!k3 && !k5) || S23 % (16 / S1)) return false;
+    // The chain's own kernel takes time in proportion to the rank, this one
+    // hardly any more per rank.  Measured, chain / merged, forward us: 8x8x8
+    // modes, 7x7, batch 32: 18 / 25 (rank 8), 28 / 26 (16), 47 / 32 (32), 85 /
+    // 44 (64); batch 1: 22 / 22 (16), 36 / 28 (32).  4x4x8 modes, 28x28, batch
+    // 32: 53 / 57 (8), 89 / 58 (16), 294 / 75 (64); batch 1: 27 / 28 (8), 45 /
+    // 28 (16).
+    if (q.R <= (k3 ? 16 : 8)) return false;
+    RcpDfwdDesc d;
+    std::memset(&d, 0, sizeof(d));
+    d.t = same_tile(q, false);
+    const int64_t px = k3 ? 64 : 256, most = k3 ? 128 : 512;   // staged slots that four units a thread cover
+    bool fits = false;
+    for (int64_t want = px; want >= 16 && !fits; want -= 16) fits = dense_tile(d.t, want) && d.t.slots <= most;
+    if (!fits || 2 * d.t.NI * q.H * q.W * S1 * S23 >= (1ll << 31)) return false;
+    d.R = (int32_t)q.R;
+    d.RK = (int32_t)((q.R + 15) / 16);
+    d.T1 = (int32_t)q.T[0]; d.T2 = (int32_t)q.T[1]; d.T3 = (int32_t)q.T[2];
+    d.S1 = (int32_t)S1; d.S2 = (int32_t)q.S[1]; d.S3 = (int32_t)q.S[2];
+    d.nch = (int32_t)(S23 / (16 / S1));
+    const int64_t tiles = (q.K * q.K + 32 / S1 - 1) / (32 / S1), PR = 16 * d.RK + 4;
+    d.o_f = 0;
+    d.o_w2 = (uint32_t)(tiles * d.RK * 1024);
+    d.o_w3 = (uint32_t)(d.o_w2 + 4 * q.T[1] * q.S[1] * PR);
+    d.o_w = (uint32_t)(d.o_w3 + 4 * q.T[2] * q.S[2] * PR);
+    d.o_x = d.o_w + (k3 ? 0 : 2 * (uint32_t)(q.K * q.K) * 1024);
+    // the eight wavefronts' buffers, then (in their place) their sums; or two shared buffers
+    const int64_t lds = d.o_x + (k3 ? std::max<int64_t>(65536, 8 * (int64_t)d.t.slots * 48) : 2 * (int64_t)d.t.slots * 48);
+    d.blocks = q.T[0] * d.t.npt;
+    if (lds > 160 * 1024 || d.blocks > 0x7fffffff) return false;
+    d.lds_bytes = (uint32_t)lds;
+    f.kind = K_RCP_DFWD | (1 << kBitIn) | (1 << kBitAux) | (1 << kBitOut);
+    f.grid[0] = (uint32_t)d.blocks;
+    f.block[0] = k3 ? 512 : 256;
+    f.lds = d.lds_bytes;
+    f.desc.resize(sizeof(d));
+    std::memcpy(f.desc.data(), &d, sizeof(d));
+    f.what = "fused RCP chain: steps 0-3 as one convolution, its kernel merged on chip";
+    f.kname = k3 ? "rcp_dfwd_k<8, 3, 4>" : "rcp_dfwd_p<4, 5, 4>";
+    return true;
+}
+
+bool dense_rcp_forward(const ce_plan& p, ScratchAlloc& scratch, std::vector<Launch>& out) {
+    RcpShape q;
+    if (p.dtype != CE_BF16 || !dense_rcp_shape(p, q)) return false;
+    // A chain of four launches streams its intermediates at about 3 TB/s, each
+    // written and read once, after some 22 us of launches; the dense form is
+    // latency-bound per (channel chunk, tap) at about 0.4 us a round of blocks
+    // (8x8x8 -> 4x4x4 modes, rank 4, 14x14, 5x5 taps, batch 8: 29 us as a
+    // chain, 47 merged; batch 40, 28x28, 3x3: 130 and 57).
+    double chain = 22.0;
+    for (size_t s = 0; s + 1 < p.steps.size(); s++) {
+        double n = 2.0;
+        for (int64_t v : p.nodes[p.steps[s].c].dims) n *= (double)v;
+        chain += 2.0 * n / 3e6;
+    }
+    std::vector<Launch> v;
+    if (!dense_rcp_conv(q, true, false, scratch, v)) return false;
+    DConvDesc d;
+    std::memcpy(&d, v[1].desc.data(), sizeof(d));
+    const double q_n = (double)(d.cfg == 2 ? (d.nch + 3) / 4 : d.nch) * (double)(q.K * q.K);
+    const double rounds = (double)((d.blocks + 255) / 256) * (d.cfg == 1 ? 0.5 : 1.0);
+    if (13.0 + 0.4 * q_n * rounds > chain) return false;
+    out.insert(out.end(), v.begin(), v.end());
+    return true;
+}
+
+bool dense_rcp_backward(const ce_plan& p, bool chain, ScratchAlloc& real, std::vector<Launch>& out) {
+    RcpShape q;
+    if (p.dtype != CE_BF16 || !dense_rcp_shape(p, q)) return false;
+    // The fused chain backward (`chain`) stays for small ranks.  Measured,
+    // chain / merged, us: 8x8x8 modes, 7x7: 80 / 79 (rank 8, batch 1), 92 / 94
+    // (rank 8, batch 32), 147 / 95 (rank 16), 478 / 99 (rank 64); 4x4x8 modes,
+    // 5x5 taps, 28x28: 64 / 75 (rank 4, batch 4), 72 / 68 (rank 8, batch 1),
+    // 171 / 125 (rank 2, batch 32), 2011 / 130 (rank 64, batch 32).  Against
+    // unfused steps the merged form won at every size tried (115 us and more
+    // against 41 to 180).
+    if (chain && (q.K == 3 ? q.R <= 8 : q.R < 8 && q.R * q.B * q.H * q.W < 50176)) return false;
+    // no more workspace than the allocation-free backward holds
+    struct Counted : ScratchAlloc {
+        ScratchAlloc& real;
+        size_t total = 0;
+        explicit Counted(ScratchAlloc& r) : real(r) {}
+        BufRef alloc(size_t bytes) override {
+            total += (bytes + 255) & ~size_t(255);
+            return real.alloc(bytes);
+        }
+    } scratch(real);
+    const bool bf16 = p.dtype == CE_BF16;
+    const int64_t S = q.S[0] * q.S[1] * q.S[2], T = q.T[0] * q.T[1] * q.T[2], HW = q.H * q.W, KT = q.K * q.K;
+    DWgradDesc w;
+    std::memset(&w, 0, sizeof(w));
+    w.t = same_tile(q, false);
+    w.T = (int32_t)T;
+    w.S = (int32_t)S;
+    w.x_sb = S * HW;
+    w.g_sb = T * HW;
+    w.x_sc = w.g_sc = HW;
+    Launch lw;
+    if (!plan_dwgrad(w, bf16, 42 << 20, lw)) return false;
+    if (!dense_rcp_conv(q, bf16, true, scratch, out)) return false;
+    auto ref = [](BufKind k, int i) {
+        BufRef b;
+        b.kind = k;
+        b.index = i;
+        return b;
+    };
+    const uint32_t fneed = (1u << q.f[0]) | (1u << q.f[1]) | (1u << q.f[2]) | (1u << q.f[3]);
+    const BufRef DW = scratch.alloc((size_t)(w.nsplit * KT * T * S) * 4);
+    lw.a = ref(BUF_DOUT, 0);
+    lw.b = ref(BUF_IN, q.X);
+    lw.d = DW;
+    lw.need = fneed;
+    lw.what = "gradient of the merged kernel: pixel-tile partials";
+    out.push_back(lw);
+    DRcpDesc m = rcp_desc(q);
+    m.nsplit = w.nsplit;
+    const int64_t T12 = q.T[0] * q.T[1];
+    tap_groups(m, T12 * m.nrc);
+    m.blocks = T12 * m.nrc * m.NJ;
+    const int64_t n1 = q.T[0] * q.S[0], n2 = q.T[1] * q.S[1], n3 = q.T[2] * q.S[2];
+    const int64_t c1 = q.T[1] * m.NJ, c2 = q.T[0] * m.NJ, c3 = T12 * m.NJ, c0 = T12;
+    const BufRef P1 = scratch.alloc((size_t)(c1 * q.R * n1) * 4), P2 = scratch.alloc((size_t)(c2 * q.R * n2) * 4);
+    const BufRef P3 = scratch.alloc((size_t)(c3 * q.R * n3) * 4), P0 = scratch.alloc((size_t)(c0 * q.R * KT) * 4);
+    Launch lf;
+    lf.kind = K_RCP_FGRAD | (bf16 ? 1 << kBitIn : 0);
+    lf.extra = {ref(BUF_IN, q.f[0]), ref(BUF_IN, q.f[1]), ref(BUF_IN, q.f[2]), ref(BUF_IN, q.f[3]), DW, P1, P2, P3, P0};
+    lf.grid[0] = (uint32_t)m.blocks;
+    lf.block[0] = 256;
+    lf.lds = (uint32_t)(4 * (128 * 68 + 64 * 65 + 64 * KT + 128));
+    lf.desc.resize(sizeof(m));
+    std::memcpy(lf.desc.data(), &m, sizeof(m));
+    lf.need = fneed;
+    lf.what = "factor gradients from the merged kernel's gradient";
+    lf.kname = bf16 ? "rcp_fgrad<unsigned short>" : "rcp_fgrad<float>";
+    lf.alg_bytes = 4.0 * w.nsplit * KT * T * S;
+    lf.alg_flops = 4.0 * (double)S * T * KT * q.R;
+    out.push_back(lf);
+    MultiReduceDesc md;
+    std::memset(&md, 0, sizeof(md));
+    md.n = 4;
+    const int64_t ns[4] = {n1, n2, n3, KT}, cs[4] = {c1, c2, c3, c0};
+    const BufRef parts[4] = {P1, P2, P3, P0};
+    Launch lr;
+    lr.kind = K_REDUCE_MULTI;
+    double rb = 0;
+    for (int j = 0; j < 4; j++) {
+        ReduceDesc& rd = md.part[j];
+        rd.M = (int32_t)q.R;
+        rd.N = (int32_t)ns[j];
+        rd.nsplit = cs[j];
+        rd.sCm = ns[j];
+        rd.sCn = 1;
+        md.block0[j + 1] = md.block0[j] + (q.R * ns[j] + 63) / 64;
+        lr.extra.push_back(parts[j]);
+        lr.extra.push_back(ref(BUF_DIN, q.f[j]));
+        rb += 4.0 * q.R * ns[j] * (cs[j] + 1);
+    }
+    const int rw = reduce_waves(std::max(std::max(c1, c2), std::max(c3, c0)));
+    lr.grid[0] = (uint32_t)md.block0[4];
+    lr.block[0] = (uint32_t)(64 * rw);
+    lr.desc.resize(sizeof(md));
+    std::memcpy(lr.desc.data(), &md, sizeof(md));
+    lr.need = fneed;
+    lr.what = "dW1, dW2, dW3, dW0: sums of block partials";
+    lr.kname = "reduce_multi<" + std::to_string(rw) + ">";
+    lr.alg_bytes = rb;
+    out.push_back(lr);
+    if (scratch.total > (size_t)CE_NOALLOC_WORKSPACE_BYTES) {
+        out.clear();
+        return false;
+    }
+    return true;
 }
 
 }  // namespace ce

@@ -61,6 +61,17 @@ hipError_t launch_rcp_fwd(const Launch& ln, const void* const* ops, void* y, hip
 hipError_t launch_rcp_bwd(const Launch& ln, const void* const* ops, hipStream_t s);
 hipError_t launch_rcp_prep(const Launch& ln, const void* const* ops, hipStream_t s);
 
+// Dense convolution with a packed kernel (K_DCONV): x = input planes, a = the
+// packed kernel, y = output planes; the partials of its kernel's gradient
+// (K_DWGRAD): g = output gradient, x = input planes, p = fp32 partials.
+hipError_t launch_dconv(const Launch& ln, const void* x, const void* a, void* y, hipStream_t s);
+hipError_t launch_dwgrad(const Launch& ln, const void* g, const void* x, void* p, hipStream_t s);
+// Merged kernel of a reshaped-CP layer: ops = {W1, W2, W3, W0, packed kernel};
+// its factor gradients: ops = {W1, W2, W3, W0, DW, P1, P2, P3, P0}.
+hipError_t launch_rcp_merge(const Launch& ln, const void* const* ops, hipStream_t s);
+hipError_t launch_rcp_dfwd(const Launch& ln, const void* const* ops, void* y, hipStream_t s);   // {X, W1, W2, W3, W0}
+hipError_t launch_rcp_fgrad(const Launch& ln, const void* const* ops, hipStream_t s);
+
 // Fused CP chain backward: ops = {X, dY, dX (may be NULL), Us, Kh, Kw, Ut,
 // Pus, Put, Pkh, Pkw}.
 hipError_t launch_cp_bwd(const Launch& ln, const void* const* ops, hipStream_t s);

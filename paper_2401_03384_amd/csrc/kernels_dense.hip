@@ -1,0 +1,1188 @@
+// Dense-kernel path: a factorised convolution evaluated through its merged
+// kernel W[t][s][kh][kw] as implicit-GEMM convolutions on MFMA tiles
+// (Section 3.1: any pairwise order computes the same layer; this one merges
+// the factors first).  For reshaped CP the factor-at-a-time chain has 4- and
+// 8-term contractions that no matrix tile fits and runs on the vector ALU;
+// the merged kernel costs more multiplications but all of them on matrix
+// cores.
+//
+//   rcp_merge  W from the factors (fp32 MFMA), packed in operand order
+//   dconv      Y = W * X, or dX = W^T * dY with the taps reversed
+//   dwgrad     partials of dW = dY x X over pixel tiles
+//   rcp_fgrad  the factors' gradients from dW (fp32 MFMA), per-block partials
+//   rcp_dfwd_* Y = W * X with W merged on chip (one launch, no workspace)
+//
+// Measured (X[32,8,8,8,7,7], 3x3, rank 64 / X[32,4,4,8,28,28], 5x5, rank 64;
+// bf16): forward 95 -> 42 us / 308 -> 77 us against the chain's vector-ALU
+// kernel, backward 465 -> 107 us / 2010 -> 137 us (merge 16 / 12, dconv 22 /
+// 44 = 340 / 470 TFLOP/s, dwgrad 27 / 47 = 270 / 440 TFLOP/s, rcp_fgrad 33 /
+// 25, sums 9 / 10).  What bounds them: dconv and dwgrad operand latency (one
+// or two wavefronts a SIMD, LDS and L2 reads of 16 bytes a lane for every one
+// or two MFMAs); rcp_merge and rcp_fgrad the set-up of their rank tables.
+#include <atomic>
+#include <cstdint>
+#include <cstring>
+#include <type_traits>
+
+#include "desc_dense.h"
+#include "hip_util.h"
+#include "kernels.h"
+
+namespace ce {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+constexpr uint32_t kOut = 0x80000000u;   // a buffer offset past every range: reads 0
+
+// acc += A (32 x k) B (k x 32) for the 16 operand bytes a lane holds: one
+// 32x32x16 bf16 MFMA, or four 32x32x2 fp32 ones (k pairs (i, 4 + i))
+template <typename T>
+__device__ __forceinline__ void mma(f32x16& acc, const uint4& a, const uint4& b) {
+    if constexpr (sizeof(T) == 2) {
+        bf16x8 x, y;
+        __builtin_memcpy(&x, &a, 16);
+        __builtin_memcpy(&y, &b, 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+    } else {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+    }
+}
+
+// the 16 bytes of one staging unit: EPU consecutive channels of one position
+template <typename T>
+struct Unit {
+    static constexpr int EPU = 16 / sizeof(T);
+    uint32_t v[EPU];
+    // voff: byte offset of the unit's first channel (kOut: zero); sc: bytes
+    // between channels; soff: wave-uniform byte offset; left: channels of the
+    // unit that exist (the rest read 0)
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int sc, int soff) {
+#pragma unroll
+        for (int e = 0; e < EPU; e++) {
+            if constexpr (sizeof(T) == 2) v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, soff + e * sc, 0);
+            else v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, soff + e * sc, 0);
+        }
+    }
+    __device__ __forceinline__ void load_part(__amdgpu_buffer_rsrc_t r, uint32_t voff, int sc, int soff, int left) {
+#pragma unroll
+        for (int e = 0; e < EPU; e++) {
+            const int vo = e < left ? (int)voff : (int)kOut;
+            const int so = soff + e * sc;
+            if constexpr (sizeof(T) == 2) v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0);
+            else v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0);
+        }
+    }
+    __device__ __forceinline__ uint4 pack() const {
+        if constexpr (sizeof(T) == 2)
+            return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+        else return make_uint4(v[0], v[1], v[2], v[3]);
+    }
+};
+
+// byte offset (in a group of NI images of stride sb, rows contiguous) of
+// staged slot `slot` of a tile starting at output row h0; kOut when outside
+template <typename T>
+__device__ __forceinline__ uint32_t slot_offset(const DTile& t, int slot, int h0, int ni, int64_t sb) {
+    const int area = t.HP * t.WP;
+    const int img = slot / area, rem = slot - img * area;
+    const int rr = rem / t.WP, cc = rem - rr * t.WP;
+    const int hh = t.sth * h0 + min(t.zh0, t.zh0 + t.zhs * (t.KH - 1)) + rr;
+    const int ww = min(t.zw0, t.zw0 + t.zws * (t.KW - 1)) + cc;
+    const bool ok = img < ni && hh >= 0 && hh < t.H && ww >= 0 && ww < t.W;
+    return ok ? (uint32_t)(sizeof(T) * (img * sb + (int64_t)hh * t.W + ww)) : kOut;
+}
+
+constexpr int kPitch = 20;   // words a staged slot takes in dconv: 64 B of channels + 16 B
+                             // (16-byte reads of 8 neighbouring slots hit distinct banks)
+
+// One block: MW * MT * 32 rows x one pixel tile (at most NW * NT * 32 pixels),
+// KS x KS taps.  A wavefront streams its packed rows from L2 (operand loads D
+// taps ahead in a register ring, D dividing the taps) against pixel operands
+// from LDS; the next chunk of channels is in flight to registers (the first
+// NU units a thread) during the current one's MFMAs.  KSP = 1: the block's
+// four wavefronts share each staged chunk (two LDS buffers, one barrier a
+// chunk).  KSP = 4 (few pixels): each wavefront takes the whole 64 x 64 tile
+// for every fourth chunk, staged by itself without block barriers, which
+// halves the operand bytes an MFMA reads against four 32 x 32 wavefronts; the
+// four sums are added in order through LDS.
+template <typename T, int KS, int KSP, int MW, int NW, int MT, int NT, int D, int NU>
+__global__ void __launch_bounds__(256, 2) dconv(DConvDesc d, const T* __restrict__ X,
+                                                const uint4* __restrict__ A, T* __restrict__ Y) {
+    constexpr int EPU = 16 / sizeof(T), CK = 4 * EPU, KT = KS * KS, NTH = 256 / KSP;
+    static_assert(KT % D == 0, "the ring restarts with every chunk");
+    static_assert(KSP == 1 || (KSP == 4 && MW == 1 && NW == 1 && MT == 2 && NT == 2), "");
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const DTile& t = d.t;
+    const int lane = threadIdx.x & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = KSP == 1 ? (int)threadIdx.x : lane;
+    const int wm = KSP == 1 ? wave % MW : 0, wn = KSP == 1 ? wave / MW : 0;
+    const int mb = (int)(blockIdx.x % (uint32_t)d.mblk), pt = (int)(blockIdx.x / (uint32_t)d.mblk);
+    const int ti = pt / t.nth, h0 = (pt - ti * t.nth) * t.TH, b0 = ti * t.NI;
+    const int ni = min(t.NI, t.B - b0), nr = min(t.TH, t.OH - h0);
+    const int slots = t.slots;
+    const int sc = (int)(sizeof(T) * d.x_sc);
+    const int mtiles = (d.M + 31) / 32;
+    // this wavefront's chunks: c0, c0 + KSP, ...; q counts its (chunk, tap)s
+    const int c0 = KSP == 1 ? 0 : wave, nmy = c0 < d.nch ? (d.nch - c0 + KSP - 1) / KSP : 0;
+    const uint4* pa[MT];
+#pragma unroll
+    for (int m = 0; m < MT; m++) {
+        const int mt = min((mb * MW + wm) * MT + m, mtiles - 1);
+        pa[m] = A + ((int64_t)mt * d.nch + min(c0, d.nch - 1)) * KT * 128 + lane;
+    }
+    uint4 a[D][MT][2];
+#pragma unroll
+    for (int q = 0; q < D; q++)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int k = 0; k < 2; k++) a[q][m][k] = pa[m][128 * q + 64 * k];
+    const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(X + b0 * d.x_sb), (short)0, (int)(sizeof(T) * ni * d.x_sb), 0x00020000);
+    uint32_t voff[NU];
+    int dst[NU], cg[NU];
+#pragma unroll
+    for (int i = 0; i < NU; i++) {
+        const int u = tid + NTH * i, g = u / slots, slot = u - g * slots;
+        const uint32_t o = u < 4 * slots ? slot_offset<T>(t, slot, h0, ni, d.x_sb) : kOut;
+        cg[i] = g;
+        voff[i] = o == kOut ? kOut : o + (uint32_t)(g * EPU * sc);
+        dst[i] = slot * kPitch + 4 * g;
+    }
+    const bool part = d.C % CK != 0;
+    Unit<T> un[NU];
+    auto fetch = [&](int ch) {
+        const int soff = ch * CK * sc;
+        if (part && ch == d.nch - 1) {
+#pragma unroll
+            for (int i = 0; i < NU; i++) un[i].load_part(rX, voff[i], sc, soff, d.C - ch * CK - cg[i] * EPU);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NU; i++) un[i].load(rX, voff[i], sc, soff);
+        }
+    };
+    if (nmy > 0) fetch(c0);
+    // pixel operands: slot of the lane's pixel of each column tile
+    int base[NT];
+    bool ok[NT];
+    int64_t yo[NT];
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+        const int n = (wn * NT + j) * 32 + cl, per = t.TH * t.OW;
+        const int img = n / per, rem = n - img * per, r = rem / t.OW, c = rem - r * t.OW;
+        ok[j] = img < ni && r < nr;
+        yo[j] = (b0 + img) * d.y_sb + (h0 + r) * d.y_sh + c * d.y_sw;
+        base[j] = (ok[j] ? (img * t.HP + t.sth * r) * t.WP + t.stw * c : 0) * kPitch + 4 * hf;
+    }
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int j = 0; j < NT; j++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) acc[m][j][i] = 0.f;
+    const int mh = min(0, t.zhs * (KS - 1)), mw = min(0, t.zws * (KS - 1));
+    uint32_t* const buf0 = KSP == 1 ? lds : lds + 2 * wave * slots * kPitch;
+    uint32_t* buf = buf0;
+    for (int n = 0; n < nmy; n++) {
+        const int ch = c0 + KSP * n;
+#pragma unroll
+        for (int i = 0; i < NU; i++)
+            if (tid + NTH * i < 4 * slots) *reinterpret_cast<uint4*>(buf + dst[i]) = un[i].pack();
+        for (int u = tid + NTH * NU; u < 4 * slots; u += NTH) {   // tiles past NU units a thread
+            const int g = u / slots, slot = u - g * slots;
+            const uint32_t o = slot_offset<T>(t, slot, h0, ni, d.x_sb);
+            Unit<T> x;
+            x.load_part(rX, o == kOut ? kOut : o + (uint32_t)(g * EPU * sc), sc, ch * CK * sc, d.C - ch * CK - g * EPU);
+            *reinterpret_cast<uint4*>(buf + slot * kPitch + 4 * g) = x.pack();
+        }
+        if constexpr (KSP == 1) {
+            __syncthreads();
+        } else {
+            // the buffer is this wavefront's own: order its LDS accesses only
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        if (n + 1 < nmy) fetch(ch + KSP);
+        const bool mask = part && ch == d.nch - 1;
+        // operands D taps on: the same chunk, else the wavefront's next one
+        const int64_t qa = (int64_t)KSP * n * KT, qb = (int64_t)KSP * min(n + 1, nmy - 1) * KT;
+#pragma unroll
+        for (int j = 0; j < KT; j++) {
+            const uint32_t* bt = buf + ((t.zhs * (j / KS) - mh) * t.WP + t.zws * (j % KS) - mw) * kPitch;
+            uint4 b[2][NT];
+#pragma unroll
+            for (int k = 0; k < 2; k++)
+#pragma unroll
+                for (int x = 0; x < NT; x++) b[k][x] = *reinterpret_cast<const uint4*>(bt + base[x] + 8 * k);
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                if (mask) {
+                    // packed channels past C hold no kernel values
+                    const int left = d.C - ch * CK - (2 * k + hf) * EPU;
+#pragma unroll
+                    for (int m = 0; m < MT; m++) {
+                        uint4& v = a[j % D][m][k];
+                        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            if constexpr (sizeof(T) == 2) {
+                                if (2 * e + 1 >= left) w[e] &= 0xffffu;
+                                if (2 * e >= left) w[e] = 0;
+                            } else if (e >= left) w[e] = 0;
+                        }
+                        v = make_uint4(w[0], w[1], w[2], w[3]);
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < MT; m++)
+#pragma unroll
+                    for (int x = 0; x < NT; x++) mma<T>(acc[m][x], a[j % D][m][k], b[k][x]);
+            }
+            const int64_t qn = (j + D < KT ? qa + j + D : qb + (j + D - KT)) * 128;
+#pragma unroll
+            for (int m = 0; m < MT; m++)
+#pragma unroll
+                for (int k = 0; k < 2; k++) a[j % D][m][k] = pa[m][qn + 64 * k];
+        }
+        buf = buf == buf0 ? buf0 + slots * kPitch : buf0;
+    }
+    // accumulator i of a lane: row 8(i / 4) + 4 hf + i % 4 of its row tile
+    auto put = [&](const f32x16& v, int m, int64_t o) {
+        const int r0 = ((mb * MW + wm) * MT + m) * 32 + 4 * hf;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = r0 + 8 * (i >> 2) + (i & 3);
+            if (r < d.M) store(Y, o + r * d.y_sm, v[i]);
+        }
+    };
+    if constexpr (KSP == 1) {
+#pragma unroll
+        for (int x = 0; x < NT; x++) {
+            if (!ok[x]) continue;
+#pragma unroll
+            for (int m = 0; m < MT; m++) put(acc[m][x], m, yo[x]);
+        }
+    } else {
+        float* red = reinterpret_cast<float*>(lds);   // [tile][wavefront][16][64]
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int x = 0; x < NT; x++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) red[((2 * m + x) * 4 + wave) * 1024 + 64 * i + lane] = acc[m][x][i];
+        __syncthreads();
+        // wavefront w: the tile of rows w / 2, columns w % 2
+        f32x16 v;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const float* p = red + wave * 4096 + 64 * i + lane;
+            v[i] = (p[0] + p[1024]) + (p[2048] + p[3072]);
+        }
+        const bool second = wave & 1;
+        if (second ? ok[1] : ok[0]) put(v, wave >> 1, second ? yo[1] : yo[0]);
+    }
+}
+
+// One block: 64 t x (32 NS) s x every tap, over its share of the pixel tiles;
+// 2 NS NTG wavefronts, each 32 t x 32 s x the taps j = tg, tg + NTG, ...
+// G and X sit in LDS position-major (channels innermost); the reduction runs
+// over pixels, so bf16 operands are read with the transposing 8-byte LDS load
+// (a group of 16 lanes: 4 pixels x 16 channels, lane l gets channel l's four
+// pixels) and fp32 ones word by word.  Pixels past a tile point at zero slots.
+// The next tile is in flight to registers (at most four units a thread of G
+// and of X, which the planner's tile respects) during the current one's MFMAs.
+template <typename T, int NS, int NTG, int TG>
+__global__ void __launch_bounds__(128 * NS * NTG, 2) dwgrad(DWgradDesc d, const T* __restrict__ G,
+                                                           const T* __restrict__ X, float* __restrict__ P) {
+    constexpr int EPU = 16 / sizeof(T), NTHR = 128 * NS * NTG;
+    constexpr int GU = 64 / EPU, XU = 32 * NS / EPU;                 // units of one pixel / slot
+    constexpr int UG = 4, UX = 4;                                    // units a thread
+    constexpr int PG = (64 * sizeof(T) + 16) / 4;                    // words a pixel
+    constexpr int PX = (32 * NS * sizeof(T) + (NS == 1 && sizeof(T) == 2 ? 32 : 16)) / 4;
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const DTile& t = d.t;
+    uint32_t* lg = lds;
+    uint32_t* lx = lds + d.o_x / 4;
+    int* tab = reinterpret_cast<int*>(lds + d.o_tab / 4);
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wt = wave & 1, ws = (wave >> 1) % NS, wg = (wave >> 1) / NS;
+    uint32_t id = blockIdx.x;
+    const int sb = (int)(id % (uint32_t)d.nsb);
+    id /= (uint32_t)d.nsb;
+    const int tb = (int)(id % (uint32_t)d.ntb), sp = (int)(id / (uint32_t)d.ntb);
+    const int t0 = tb * 64, s0 = sb * 32 * NS;
+    const int KT = t.KH * t.KW, slots = t.slots, per = t.TH * t.OW;
+    const int gsc = (int)(sizeof(T) * d.g_sc), xsc = (int)(sizeof(T) * d.x_sc);
+    // zero slots after the tile: every tap of a pixel past the tile reads there
+    const int zspan = (t.KH - 1) * t.WP + t.KW;
+    for (int u = tid; u < zspan * PX; u += NTHR) lx[slots * PX + u] = 0;
+    int toff[TG];
+    const int mh = min(0, t.zhs * (t.KH - 1)), mw = min(0, t.zws * (t.KW - 1));
+#pragma unroll
+    for (int a = 0; a < TG; a++) {
+        const int j = min(wg + a * NTG, KT - 1), ji = j / t.KW, jj = j - ji * t.KW;
+        toff[a] = ((t.zhs * ji - mh) * t.WP + t.zws * jj - mw) * PX;
+    }
+    // a thread's staging units, the same for every tile: byte offset from the
+    // tile's first row of its first image, image, row; LDS word
+    int goff[UG], gim[UG], gr[UG], gdst[UG], gch[UG];
+    int xoff[UX], xim[UX], xr[UX], xdst[UX], xch[UX];
+    const int hmin = min(t.zh0, t.zh0 + t.zhs * (t.KH - 1)), wmin = min(t.zw0, t.zw0 + t.zws * (t.KW - 1));
+#pragma unroll
+    for (int i = 0; i < UG; i++) {
+        const int u = tid + i * NTHR, g = u / d.PP, px = u - g * d.PP;
+        const int img = px / per, rem = px - img * per;
+        gr[i] = rem / t.OW;
+        gim[i] = u < GU * d.PP ? img : 0x7fffffff;
+        gch[i] = t0 + g * EPU;
+        goff[i] = (int)(sizeof(T) * (img * d.g_sb + rem)) + gch[i] * gsc;
+        gdst[i] = u < GU * d.PP ? px * PG + 4 * g : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < UX; i++) {
+        const int u = tid + i * NTHR, g = u / slots, slot = u - g * slots;
+        const int area = t.HP * t.WP, img = slot / area, rem = slot - img * area;
+        const int rr = rem / t.WP, ww = wmin + rem - rr * t.WP;
+        xr[i] = hmin + rr;
+        xim[i] = u < XU * slots && ww >= 0 && ww < t.W ? img : 0x7fffffff;
+        xch[i] = s0 + g * EPU;
+        xoff[i] = (int)(sizeof(T) * (img * d.x_sb + xr[i] * t.W + ww)) + xch[i] * xsc;
+        xdst[i] = u < XU * slots ? slot * PX + 4 * g : -1;
+    }
+    const int pimg = tid / per, prem = tid - pimg * per, prow = prem / t.OW;
+    const int pslot = ((pimg * t.HP + t.sth * prow) * t.WP + t.stw * (prem - prow * t.OW)) * PX;
+    f32x16 acc[TG];
+#pragma unroll
+    for (int a = 0; a < TG; a++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[a][i] = 0.f;
+    const int p0 = (int)((int64_t)t.npt * sp / d.nsplit), p1 = (int)((int64_t)t.npt * (sp + 1) / d.nsplit);
+    Unit<T> ug[UG], ux[UX];
+    int ni = 0, nr = 0;
+    auto fetch = [&](int pt) {
+        const int ti = pt / t.nth, h0 = (pt - ti * t.nth) * t.TH, b0 = ti * t.NI;
+        ni = min(t.NI, t.B - b0);
+        nr = min(t.TH, t.OH - h0);
+        const __amdgpu_buffer_rsrc_t rG = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(G + b0 * d.g_sb), (short)0, (int)(sizeof(T) * ni * d.g_sb), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(X + b0 * d.x_sb), (short)0, (int)(sizeof(T) * ni * d.x_sb), 0x00020000);
+        const int gh = (int)sizeof(T) * h0 * t.OW, xh0 = t.sth * h0, xh = (int)sizeof(T) * xh0 * t.W;
+#pragma unroll
+        for (int i = 0; i < UG; i++)
+            if (i * NTHR < GU * d.PP) ug[i].load_part(rG, gim[i] < ni && gr[i] < nr ? (uint32_t)(goff[i] + gh) : kOut, gsc, 0, d.T - gch[i]);
+#pragma unroll
+        for (int i = 0; i < UX; i++) {
+            if (i * NTHR >= XU * slots) break;
+            const bool in = xim[i] < ni && xr[i] + xh0 >= 0 && xr[i] + xh0 < t.H;
+            ux[i].load_part(rX, in ? (uint32_t)(xoff[i] + xh) : kOut, xsc, 0, d.S - xch[i]);
+        }
+    };
+    if (p0 < p1) fetch(p0);
+    for (int pt = p0; pt < p1; pt++) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < UG; i++)
+            if (gdst[i] >= 0) *reinterpret_cast<uint4*>(lg + gdst[i]) = ug[i].pack();
+#pragma unroll
+        for (int i = 0; i < UX; i++)
+            if (xdst[i] >= 0) *reinterpret_cast<uint4*>(lx + xdst[i]) = ux[i].pack();
+        if (tid < d.PP) tab[tid] = pimg < ni && prow < nr ? pslot : slots * PX;
+        __syncthreads();
+        if (pt + 1 < p1) fetch(pt + 1);
+        if constexpr (sizeof(T) == 2) {
+            const int g16 = lane >> 4, i16 = lane & 15;
+            const int choff = (16 * (g16 & 1) + 4 * (i16 & 3)) / 2;   // words
+            const uint32_t* ga = lg + 16 * wt + choff;
+            const uint32_t* xa = lx + 16 * ws + choff;
+            const int kp = 8 * hf + (i16 >> 2);
+            typedef __attribute__((address_space(3))) s16x4* lptr;
+            auto tr = [](const uint32_t* p, const uint32_t* q) {
+                const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)p);
+                const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)q);
+                uint4 w;
+                __builtin_memcpy(&w.x, &u, 8);
+                __builtin_memcpy(&w.z, &v, 8);
+                return w;
+            };
+            for (int k = 0; k < d.PP; k += 16) {
+                const int pa = k + kp, s_a = tab[pa], s_b = tab[pa + 4];
+                const uint4 av = tr(ga + pa * PG, ga + (pa + 4) * PG);
+                const uint32_t* x0 = xa + s_a;
+                const uint32_t* x1 = xa + s_b;
+#pragma unroll
+                for (int a = 0; a < TG; a++) mma<T>(acc[a], av, tr(x0 + toff[a], x1 + toff[a]));
+            }
+        } else {
+            const float* ga = reinterpret_cast<const float*>(lg) + 32 * wt + cl;
+            const float* xa = reinterpret_cast<const float*>(lx) + 32 * ws + cl;
+#pragma unroll 2
+            for (int k = 0; k < d.PP; k += 2) {
+                const int p = k + hf;
+                const float av = ga[p * PG];
+                const float* x0 = xa + tab[p];
+#pragma unroll
+                for (int a = 0; a < TG; a++) acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, x0[toff[a]], acc[a], 0, 0, 0);
+            }
+        }
+    }
+    // columns s (the lane), rows t: partial [sp][tap][t][s]
+    const int s = s0 + 32 * ws + cl;
+#pragma unroll
+    for (int a = 0; a < TG; a++) {
+        const int j = wg + a * NTG;
+        if (j >= KT || s >= d.S) continue;
+        float* o = P + ((int64_t)sp * KT + j) * d.T * d.S + s;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = t0 + 32 * wt + 8 * (i >> 2) + 4 * hf + (i & 3);
+            if (r < d.T) o[(int64_t)r * d.S] = acc[a][i];
+        }
+    }
+}
+
+// Reshaped-CP forward in one launch without workspace: Y = W * X with the rows
+// of W merged on chip.  For fixed t1 and (s2, s3), over the ranks:
+//   W[t2 t3][s1, tap] = sum_r (W1[r][t1][s1] W0[r][tap]) (W2[r][t2][s2] W3[r][t3][s3])
+// is an MFMA product with rows (s1, tap) and columns (t2, t3) whose
+// accumulators, rounded to bf16, are the convolution's A operands as they
+// stand (lane = row t2 t3; its registers = s1 of a lane half, by tap).  The
+// 16-bit products of the right factor enter as an exact high + low pair, so
+// a value is rounded once in the left factor and once in W.
+template <int S1, int KS>
+struct Merge {
+    static constexpr int KT = KS * KS;
+    static constexpr int TPT = 32 / S1;                 // taps a merge tile holds
+    static constexpr int NTL = (KT + TPT - 1) / TPT;    // merge tiles
+    static constexpr int NX = 16 / S1;                  // (s2, s3) pairs of 16 channels
+    static constexpr int WPX = 4 / NX;                  // operand words a pair gives
+    static constexpr int PX = 12;                       // words a staged slot takes: 32 B of channels + 16 B
+
+    // rank tables in LDS: the left factor in operand order [tile][rank
+    // step][lane], row (s1, tap); the right ones as [s][t][rank]
+    template <int NTHR>
+    static __device__ __forceinline__ void tables(const RcpDfwdDesc& d, int t1, const bf16_t* W1, const bf16_t* W2,
+                                                  const bf16_t* W3, const bf16_t* W0, uint4* lf, float* w2, float* w3) {
+        const int RK = d.RK, PR = 16 * RK + 4, tid = threadIdx.x;
+        for (int u = tid; u < NTL * RK * 64; u += NTHR) {
+            const int l = u & 63, ks = (u >> 6) % RK, tl = (u >> 6) / RK, row = l & 31;
+            const int s1 = S1 == 8 ? row & 7 : 2 * ((row >> 2) & 1) + (row & 1);
+            const int tap = tl * TPT + (S1 == 8 ? row >> 3 : 2 * (row >> 3) + ((row >> 1) & 1));
+            float x[8], y[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const int rr = min(16 * ks + 8 * (l >> 5) + e, d.R - 1);
+                x[e] = load(W1, (rr * d.T1 + t1) * S1 + s1);
+                y[e] = load(W0, rr * KT + min(tap, KT - 1));
+            }
+            const int live = tap < KT ? d.R - (16 * ks + 8 * (l >> 5)) : 0;
+#pragma unroll
+            for (int e = 0; e < 8; e++) x[e] = e < live ? x[e] * y[e] : 0.f;
+            lf[u] = make_uint4(pk_bf16(x[0], x[1]), pk_bf16(x[2], x[3]), pk_bf16(x[4], x[5]), pk_bf16(x[6], x[7]));
+        }
+        // eight loads a thread in flight
+        auto right = [&](const bf16_t* W, float* tab, int nt, int ns) {
+            const int n = nt * ns, live = n * d.R;
+            for (int u0 = tid; u0 < n * 16 * RK; u0 += 8 * NTHR) {
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; i++) v[i] = load(W, min(u0 + NTHR * i, live - 1));
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    const int u = u0 + NTHR * i, r = u / n, x = u - r * n, a = x / ns, c = x - a * ns;
+                    if (u < n * 16 * RK) tab[(c * nt + a) * PR + r] = u < live ? v[i] : 0.f;
+                }
+            }
+        };
+        right(W2, w2, d.T2, d.S2);
+        right(W3, w3, d.T3, d.S3);
+    }
+
+    // merge tiles of one (s2, s3) and the lane's (t2, t3): p2, p3 = the
+    // lane's rank rows (8 ranks a half of every 16)
+    static __device__ __forceinline__ void pair(int RK, const float* p2, const float* p3, const uint4* lf, int lane,
+                                                f32x16 (&g)[NTL]) {
+#pragma unroll
+        for (int q = 0; q < NTL; q++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) g[q][i] = 0.f;
+#pragma unroll 2
+        for (int ks = 0; ks < RK; ks++) {
+            uint4 f[NTL];
+#pragma unroll
+            for (int q = 0; q < NTL; q++) f[q] = lf[(q * RK + ks) * 64 + lane];
+            float a[8], b[8], lo[8];
+            *reinterpret_cast<float4*>(a) = *reinterpret_cast<const float4*>(p2 + 16 * ks);
+            *reinterpret_cast<float4*>(a + 4) = *reinterpret_cast<const float4*>(p2 + 16 * ks + 4);
+            *reinterpret_cast<float4*>(b) = *reinterpret_cast<const float4*>(p3 + 16 * ks);
+            *reinterpret_cast<float4*>(b + 4) = *reinterpret_cast<const float4*>(p3 + 16 * ks + 4);
+            uint32_t hw[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const float v = a[e] * b[e];
+                hw[e] = __float_as_uint(v);
+                lo[e] = v - __uint_as_float(hw[e] & 0xffff0000u);
+            }
+            // the high halves as they are (truncated), the exact rest
+            const uint4 gh = make_uint4(__builtin_amdgcn_perm(hw[1], hw[0], 0x07060302u),
+                                        __builtin_amdgcn_perm(hw[3], hw[2], 0x07060302u),
+                                        __builtin_amdgcn_perm(hw[5], hw[4], 0x07060302u),
+                                        __builtin_amdgcn_perm(hw[7], hw[6], 0x07060302u));
+            const uint4 gl = make_uint4(pk_bf16(lo[0], lo[1]), pk_bf16(lo[2], lo[3]),
+                                        pk_bf16(lo[4], lo[5]), pk_bf16(lo[6], lo[7]));
+#pragma unroll
+            for (int q = 0; q < NTL; q++) mma<bf16_t>(g[q], f[q], gh);
+#pragma unroll
+            for (int q = 0; q < NTL; q++) mma<bf16_t>(g[q], f[q], gl);
+        }
+    }
+
+    // operand word i (of WPX) of tap j from its merge tiles
+    static __device__ __forceinline__ uint32_t word(const f32x16 (&g)[NTL], int j, int i) {
+        const int q = j / TPT, y = j % TPT, o = 2 * (WPX * y + i);
+        return pk_bf16(g[q][o], g[q][o + 1]);
+    }
+};
+
+// byte offset of channel element e (of a lane half's 8) of 16-channel chunk ch
+template <int S1>
+__device__ __forceinline__ int chan_off(int e, int ch, int S23, int HW) {
+    return 2 * HW * ((e % (S1 / 2)) * S23 + e / (S1 / 2) + ch * (16 / S1));
+}
+
+// Few pixels a block: 64 rows x at most 64 pixels, eight wavefronts that split
+// the 16-channel chunks, each staging and merging its own, without block
+// barriers; their sums are added in a fixed order through LDS.
+template <int S1, int KS, int NU>
+__global__ void __launch_bounds__(512, 2) rcp_dfwd_k(RcpDfwdDesc d, const bf16_t* __restrict__ X,
+                                                     const bf16_t* __restrict__ W1, const bf16_t* __restrict__ W2,
+                                                     const bf16_t* __restrict__ W3, const bf16_t* __restrict__ W0,
+                                                     bf16_t* __restrict__ Y) {
+    typedef bf16_t T;
+    typedef Merge<S1, KS> MG;
+    constexpr int KT = KS * KS, NX = MG::NX, PX = MG::PX, MT = 2, NT = 2;
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const DTile& t = d.t;
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t1 = (int)(blockIdx.x % (uint32_t)d.T1), pt = (int)(blockIdx.x / (uint32_t)d.T1);
+    const int ti = pt / t.nth, h0 = (pt - ti * t.nth) * t.TH, b0 = ti * t.NI;
+    const int ni = min(t.NI, t.B - b0), nr = min(t.TH, t.OH - h0);
+    const int slots = t.slots, S23 = d.S2 * d.S3, T23 = d.T2 * d.T3, RK = d.RK, PR = 16 * RK + 4;
+    const int HW = t.H * t.W;
+    const int64_t x_sb = (int64_t)S1 * S23 * HW;
+    uint4* lf = reinterpret_cast<uint4*>(lds + d.o_f / 4);
+    float* w2 = reinterpret_cast<float*>(lds + d.o_w2 / 4);   // [s2][t2][rank]
+    float* w3 = reinterpret_cast<float*>(lds + d.o_w3 / 4);   // [s3][t3][rank]
+    uint32_t* buf = lds + d.o_x / 4 + wave * slots * PX;
+    const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(X + b0 * x_sb), (short)0, (int)(sizeof(T) * ni * x_sb), 0x00020000);
+    // units of this wavefront: unit g = the 8 channels of lane half g
+    uint32_t voff[NU];
+#pragma unroll
+    for (int i = 0; i < NU; i++) {
+        const int u = lane + 64 * i, g = u / slots, slot = u - g * slots;
+        const uint32_t o = u < 2 * slots ? slot_offset<T>(t, slot, h0, ni, x_sb) : kOut;
+        voff[i] = o == kOut ? kOut : o + (uint32_t)(2 * HW * g * (S1 / 2) * S23);
+    }
+    Unit<T> un[NU];
+    auto fetch = [&](int ch) {
+#pragma unroll
+        for (int i = 0; i < NU; i++) {
+            if (64 * i >= 2 * slots) break;
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                un[i].v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rX, (int)voff[i], chan_off<S1>(e, ch, S23, HW), 0);
+        }
+    };
+    if (wave < d.nch) fetch(wave);
+    MG::template tables<512>(d, t1, W1, W2, W3, W0, lf, w2, w3);
+    int base[NT];
+    bool ok[NT];
+    int64_t yo[NT];
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+        const int n = j * 32 + cl, per = t.TH * t.OW;
+        const int img = n / per, rem = n - img * per, r = rem / t.OW, c = rem - r * t.OW;
+        ok[j] = img < ni && r < nr;
+        yo[j] = ((int64_t)(b0 + img) * d.T1 + t1) * T23 * HW + (h0 + r) * t.OW + c;
+        base[j] = (ok[j] ? (img * t.HP + r) * t.WP + c : 0) * PX + 4 * hf;
+    }
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int j = 0; j < NT; j++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) acc[m][j][i] = 0.f;
+    __syncthreads();
+    for (int ch = wave; ch < d.nch; ch += 8) {
+#pragma unroll
+        for (int i = 0; i < NU; i++) {
+            const int u = lane + 64 * i, g = u / slots, slot = u - g * slots;
+            if (u < 2 * slots) *reinterpret_cast<uint4*>(buf + slot * PX + 4 * g) = un[i].pack();
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (ch + 8 < d.nch) fetch(ch + 8);
+#pragma unroll
+        for (int m = 0; m < MT; m++) {
+            const int c = min(32 * m + cl, T23 - 1), c2 = c / d.T3, c3 = c - c2 * d.T3;
+            uint32_t w[KT][4];
+#pragma unroll
+            for (int x = 0; x < NX; x++) {
+                const int s23 = ch * NX + x, s2 = s23 / d.S3, s3 = s23 - s2 * d.S3;
+                f32x16 g[MG::NTL];
+                MG::pair(RK, w2 + (s2 * d.T2 + c2) * PR + 8 * hf, w3 + (s3 * d.T3 + c3) * PR + 8 * hf, lf, lane, g);
+#pragma unroll
+                for (int j = 0; j < KT; j++)
+#pragma unroll
+                    for (int i = 0; i < MG::WPX; i++) w[j][MG::WPX * x + i] = MG::word(g, j, i);
+            }
+#pragma unroll
+            for (int j = 0; j < KT; j++) {
+                const uint32_t* bt = buf + ((j / KS) * t.WP + j % KS) * PX;
+                const uint4 av = make_uint4(w[j][0], w[j][1], w[j][2], w[j][3]);
+#pragma unroll
+                for (int x = 0; x < NT; x++) mma<T>(acc[m][x], av, *reinterpret_cast<const uint4*>(bt + base[x]));
+            }
+        }
+    }
+    // [tile][wavefront % 4][16][64]: the upper four wavefronts' sums into the
+    // lower ones, then the four
+    float* red = reinterpret_cast<float*>(lds + d.o_x / 4);
+    auto slot_of = [&](int m, int x) { return red + ((NT * m + x) * 4 + (wave & 3)) * 1024 + lane; };
+    __syncthreads();
+    if (wave >= 4)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int x = 0; x < NT; x++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) slot_of(m, x)[64 * i] = acc[m][x][i];
+    __syncthreads();
+    if (wave < 4)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int x = 0; x < NT; x++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    float* p = slot_of(m, x) + 64 * i;   // this lane's own element
+                    *p += acc[m][x][i];
+                }
+    __syncthreads();
+    // wavefront w: half the rows of tile w / 2
+    const int mw = wave >> 2, xw = (wave >> 1) & 1, i0 = 8 * (wave & 1);
+    const bool okw = xw ? ok[1] : ok[0];
+    const int64_t yw = xw ? yo[1] : yo[0];
+    if (okw)
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const float* p = red + (wave >> 1) * 4096 + 64 * (i0 + i) + lane;
+            const int r = 32 * mw + 8 * ((i0 + i) >> 2) + 4 * hf + (i & 3);
+            if (r < T23) store(Y, yw + (int64_t)r * HW, (p[0] + p[1024]) + (p[2048] + p[3072]));
+        }
+}
+
+// Many pixels: 32 rows x at most 256 pixels, four wavefronts.  Per 16-channel
+// chunk wavefront x merges the kernel values of pair x for every tap into LDS,
+// in operand order, then each convolves its 64 pixels; X chunks and merged
+// values are double-buffered, one barrier a chunk: a chunk's convolution and
+// the next one's merge run between two barriers.
+template <int S1, int KS, int NU>
+__global__ void __launch_bounds__(256, 2) rcp_dfwd_p(RcpDfwdDesc d, const bf16_t* __restrict__ X,
+                                                     const bf16_t* __restrict__ W1, const bf16_t* __restrict__ W2,
+                                                     const bf16_t* __restrict__ W3, const bf16_t* __restrict__ W0,
+                                                     bf16_t* __restrict__ Y) {
+    typedef bf16_t T;
+    typedef Merge<S1, KS> MG;
+    constexpr int KT = KS * KS, NX = MG::NX, PX = MG::PX, NT = 2;
+    static_assert(NX == 4, "a pair a wavefront");
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const DTile& t = d.t;
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t1 = (int)(blockIdx.x % (uint32_t)d.T1), pt = (int)(blockIdx.x / (uint32_t)d.T1);
+    const int ti = pt / t.nth, h0 = (pt - ti * t.nth) * t.TH, b0 = ti * t.NI;
+    const int ni = min(t.NI, t.B - b0), nr = min(t.TH, t.OH - h0);
+    const int slots = t.slots, S23 = d.S2 * d.S3, T23 = d.T2 * d.T3, RK = d.RK, PR = 16 * RK + 4;
+    const int HW = t.H * t.W;
+    const int64_t x_sb = (int64_t)S1 * S23 * HW;
+    uint4* lf = reinterpret_cast<uint4*>(lds + d.o_f / 4);
+    float* w2 = reinterpret_cast<float*>(lds + d.o_w2 / 4);   // [s2][t2][rank]
+    float* w3 = reinterpret_cast<float*>(lds + d.o_w3 / 4);   // [s3][t3][rank]
+    uint32_t* lw = lds + d.o_w / 4;                           // [2][tap][lane][4]
+    uint32_t* lx = lds + d.o_x / 4;                           // [2][slot]
+    const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(X + b0 * x_sb), (short)0, (int)(sizeof(T) * ni * x_sb), 0x00020000);
+    uint32_t voff[NU];
+    int dst[NU];
+#pragma unroll
+    for (int i = 0; i < NU; i++) {
+        const int u = tid + 256 * i, g = u / slots, slot = u - g * slots;
+        const uint32_t o = u < 2 * slots ? slot_offset<T>(t, slot, h0, ni, x_sb) : kOut;
+        voff[i] = o == kOut ? kOut : o + (uint32_t)(2 * HW * g * (S1 / 2) * S23);
+        dst[i] = u < 2 * slots ? slot * PX + 4 * g : -1;
+    }
+    Unit<T> un[NU];
+    auto fetch = [&](int ch) {
+#pragma unroll
+        for (int i = 0; i < NU; i++) {
+            if (256 * i >= 2 * slots) break;
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                un[i].v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rX, (int)voff[i], chan_off<S1>(e, ch, S23, HW), 0);
+        }
+    };
+    fetch(0);
+    MG::template tables<256>(d, t1, W1, W2, W3, W0, lf, w2, w3);
+    int base[NT];
+    bool ok[NT];
+    int64_t yo[NT];
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+        const int n = (wave * NT + j) * 32 + cl, per = t.TH * t.OW;
+        const int img = n / per, rem = n - img * per, r = rem / t.OW, c = rem - r * t.OW;
+        ok[j] = img < ni && r < nr;
+        yo[j] = ((int64_t)(b0 + img) * d.T1 + t1) * T23 * HW + (h0 + r) * t.OW + c;
+        base[j] = (ok[j] ? (img * t.HP + r) * t.WP + c : 0) * PX + 4 * hf;
+    }
+    const int c = min(cl, T23 - 1), c2 = c / d.T3, c3 = c - c2 * d.T3;
+    f32x16 acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; j++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[j][i] = 0.f;
+    auto stage = [&](int ch) {   // chunk ch's X to its buffer, its merged values to theirs
+        uint32_t* bx = lx + (ch & 1) * slots * PX;
+#pragma unroll
+        for (int i = 0; i < NU; i++)
+            if (dst[i] >= 0) *reinterpret_cast<uint4*>(bx + dst[i]) = un[i].pack();
+        if (ch + 1 < d.nch) fetch(ch + 1);
+        const int s23 = ch * NX + wave, s2 = s23 / d.S3, s3 = s23 - s2 * d.S3;
+        f32x16 g[MG::NTL];
+        MG::pair(RK, w2 + (s2 * d.T2 + c2) * PR + 8 * hf, w3 + (s3 * d.T3 + c3) * PR + 8 * hf, lf, lane, g);
+        uint32_t* bw = lw + (ch & 1) * KT * 256 + lane * 4 + wave;
+#pragma unroll
+        for (int j = 0; j < KT; j++) bw[j * 256] = MG::word(g, j, 0);
+    };
+    __syncthreads();
+    stage(0);
+    __syncthreads();
+    for (int ch = 0; ch < d.nch; ch++) {
+        const uint32_t* bx = lx + (ch & 1) * slots * PX;
+        const uint32_t* bw = lw + (ch & 1) * KT * 256 + lane * 4;
+#pragma unroll
+        for (int j = 0; j < KT; j++) {
+            const uint32_t* bt = bx + ((j / KS) * t.WP + j % KS) * PX;
+            const uint4 av = *reinterpret_cast<const uint4*>(bw + j * 256);
+#pragma unroll
+            for (int x = 0; x < NT; x++) mma<T>(acc[x], av, *reinterpret_cast<const uint4*>(bt + base[x]));
+        }
+        if (ch + 1 < d.nch) stage(ch + 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int x = 0; x < NT; x++) {
+        if (!ok[x]) continue;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = 8 * (i >> 2) + 4 * hf + (i & 3);
+            if (r < T23) store(Y, yo[x] + (int64_t)r * HW, acc[x][i]);
+        }
+    }
+}
+
+constexpr int kRP = 68;   // words a row of 64 takes in the rank tables
+
+// ranks r0 .. r0 + 63 of W1[.][t1][s1] W2[.][t2][s2] as tab[rank][s1 S2 + s2],
+// zero past R and past S1 S2
+template <typename T>
+__device__ __forceinline__ void pair_table(const DRcpDesc& d, const T* W1, const T* W2, int t1, int t2, int r0,
+                                           float* tab) {
+    const int S12 = d.S1 * d.S2;
+    const int m = threadIdx.x & 63, mm = min(m, S12 - 1), s1 = mm / d.S2, s2 = mm - s1 * d.S2;
+    const T* p1 = W1 + t1 * d.S1 + s1;
+    const T* p2 = W2 + t2 * d.S2 + s2;
+    float x[16], y[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int rr = min(r0 + (int)(threadIdx.x >> 6) + 4 * i, d.R - 1);
+        x[i] = load(p1, (int64_t)rr * d.T1 * d.S1);
+        y[i] = load(p2, (int64_t)rr * d.T2 * d.S2);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int r = (int)(threadIdx.x >> 6) + 4 * i;
+        tab[r * kRP + m] = r0 + r < d.R && m < S12 ? x[i] * y[i] : 0.f;
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void mode3_table(const DRcpDesc& d, const T* W3, const T* W0, int r0, float* w3, float* w0) {
+    const int N = d.T3 * d.S3;
+    const int n = threadIdx.x & 63;
+    float x[16], y[8];
+#pragma unroll
+    for (int i = 0; i < 16; i++)
+        x[i] = load(W3, (int64_t)min(r0 + (int)(threadIdx.x >> 6) + 4 * i, d.R - 1) * N + min(n, N - 1));
+    // KT <= 28: at most seven of the 64 KT taps a thread; rank-major, so the
+    // table is a run of the factor
+    const int live = min(64, d.R - r0) * d.KT;
+#pragma unroll
+    for (int i = 0; i < 8; i++) y[i] = load(W0, (int64_t)r0 * d.KT + min((int)threadIdx.x + 256 * i, live - 1));
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int r = (int)(threadIdx.x >> 6) + 4 * i;
+        w3[r * kRP + n] = r0 + r < d.R && n < N ? x[i] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int u = threadIdx.x + 256 * i;
+        if (u < 64 * d.KT) w0[u] = u < live ? y[i] : 0.f;
+    }
+}
+
+// W for one (t1, t2) and a group of taps: per tap a [s1 s2] x [t3 s3] tile,
+// 64 x 64, reduced over the ranks by fp32 MFMA (exact products of bf16
+// factors, one rounding at the end); the packed kernel in dconv's order.
+template <typename T>
+__global__ void __launch_bounds__(256) rcp_merge(DRcpDesc d, const T* __restrict__ W1, const T* __restrict__ W2,
+                                                 const T* __restrict__ W3, const T* __restrict__ W0,
+                                                 T* __restrict__ out) {
+    constexpr int EPU = 16 / sizeof(T);
+    extern __shared__ __attribute__((aligned(16))) float ft[];
+    float* ta = ft;
+    float* t3 = ft + 64 * kRP;
+    float* t0 = ft + 128 * kRP;
+    const int jg = (int)(blockIdx.x % (uint32_t)d.NJ), t12 = (int)(blockIdx.x / (uint32_t)d.NJ);
+    const int a1 = t12 / d.T2, a2 = t12 - a1 * d.T2;
+    const int lane = threadIdx.x & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave & 1, wn = wave >> 1;
+    const int j0 = jg * d.jper, j1 = min(d.KT, j0 + d.jper);
+    const int n = 32 * wn + cl, b3 = n / d.S3, c3 = n - b3 * d.S3, S12 = d.S1 * d.S2;
+    const bool nok = n < d.T3 * d.S3;
+    if (d.nrc == 1) {
+        pair_table(d, W1, W2, a1, a2, 0, ta);
+        mode3_table(d, W3, W0, 0, t3, t0);
+        __syncthreads();
+    }
+    for (int j = j0; j < j1; j++) {
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[i] = 0.f;
+        for (int rc = 0; rc < d.nrc; rc++) {
+            if (d.nrc > 1) {
+                __syncthreads();
+                pair_table(d, W1, W2, a1, a2, 64 * rc, ta);
+                mode3_table(d, W3, W0, 64 * rc, t3, t0);
+                __syncthreads();
+            }
+            const int kn = min(64, d.R - 64 * rc);   // table rows past R are zero
+            for (int k0 = 0; k0 < kn; k0 += 16) {
+                float a[8], b[8], c[8];
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    const int r = k0 + 2 * k + hf;
+                    a[k] = ta[r * kRP + 32 * wm + cl];
+                    b[k] = t3[r * kRP + n];
+                    c[k] = t0[r * d.KT + j];
+                }
+#pragma unroll
+                for (int k = 0; k < 8; k++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[k], b[k] * c[k], acc, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int m = 32 * wm + 8 * (i >> 2) + 4 * hf + (i & 3);
+            if (!nok || m >= S12) continue;
+            const int tt = t12 * d.T3 + b3, ss = m * d.S3 + c3;
+            const int row = d.transposed ? ss : tt, c = d.transposed ? tt : ss;
+            const int ch = c / (4 * EPU), u = (c / EPU) & 3, e = c % EPU;   // chunk, 16-byte unit in it, element
+            const int64_t o = (((int64_t)(row >> 5) * d.nch + ch) * d.KT + j) * 128 + (u >> 1) * 64 + (u & 1) * 32 + (row & 31);
+            store(out, o * EPU + e, acc[i]);
+        }
+    }
+}
+
+// Factor gradients of one (t1, t2), one group of taps, 64 ranks: per tap the
+// 64 x 64 tile D[s1 s2][t3 s3] of dW (its partials summed while loading), then
+//   dA[r][m] += W0[r][j] sum_n W3[r][n] D[m][n],  dB[r][n] = sum_m A[r][m] D[m][n]
+// on fp32 MFMA tiles; dW3 += W0 dB, dW0[j] = <W3, dB>, and at the end dW1 and
+// dW2 from dA.  Each block writes its own partials (summed in order later).
+template <typename T>
+__global__ void __launch_bounds__(256) rcp_fgrad(DRcpDesc d, const T* __restrict__ W1, const T* __restrict__ W2,
+                                                 const T* __restrict__ W3, const T* __restrict__ W0,
+                                                 const float* __restrict__ DW, float* __restrict__ P1,
+                                                 float* __restrict__ P2, float* __restrict__ P3, float* __restrict__ P0) {
+    extern __shared__ __attribute__((aligned(16))) float ft[];
+    float* ta = ft;                      // [rank][s1 s2]
+    float* t3 = ft + 64 * kRP;           // [rank][t3 s3]
+    float* td = ft + 128 * kRP;          // [s1 s2][t3 s3], odd pitch
+    constexpr int PD = 65;
+    float* t0 = td + 64 * PD;            // [rank][tap]
+    float* q0 = t0 + 64 * d.KT;          // [tile column half][rank]
+    uint32_t id = blockIdx.x;
+    const int jg = (int)(id % (uint32_t)d.NJ);
+    id /= (uint32_t)d.NJ;
+    const int rc = (int)(id % (uint32_t)d.nrc), t12 = (int)(id / (uint32_t)d.nrc);
+    const int a1 = t12 / d.T2, a2 = t12 - a1 * d.T2, r0 = 64 * rc;
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave & 1, wc = wave >> 1;
+    const int j0 = jg * d.jper, j1 = min(d.KT, j0 + d.jper);
+    const int S12 = d.S1 * d.S2, N = d.T3 * d.S3, S = S12 * d.S3;
+    const int64_t TS = (int64_t)d.T1 * d.T2 * d.T3 * S;
+    pair_table(d, W1, W2, a1, a2, r0, ta);
+    mode3_table(d, W3, W0, r0, t3, t0);
+    // D tile elements of this thread: s fastest (lanes read consecutive s)
+    const int nel = S * d.T3;
+    for (int u = tid; u < 64 * PD; u += 256) td[u] = 0.f;
+    f32x16 da, w3;
+#pragma unroll
+    for (int i = 0; i < 16; i++) da[i] = w3[i] = 0.f;
+    const float* dw0 = DW + (int64_t)t12 * d.T3 * S;
+    const int cn = 32 * wc + cl;
+    // D of tap j: NS partials of NE elements a thread in flight at once
+    auto load_tile = [&](auto ns, auto ne, int j) {
+        constexpr int NS = decltype(ns)::value, NE = decltype(ne)::value;
+        for (int u0 = tid; u0 < nel; u0 += NE * 256) {
+            float v[NE];
+#pragma unroll
+            for (int i = 0; i < NE; i++) v[i] = 0.f;
+            for (int sp = 0; sp < d.nsplit; sp += NS) {
+                float x[NS][NE];
+#pragma unroll
+                for (int q = 0; q < NS; q++) {
+                    const float* p = dw0 + ((int64_t)min(sp + q, d.nsplit - 1) * d.KT + j) * TS;
+#pragma unroll
+                    for (int i = 0; i < NE; i++) x[q][i] = p[min(u0 + 256 * i, nel - 1)];
+                }
+#pragma unroll
+                for (int q = 0; q < NS; q++)
+#pragma unroll
+                    for (int i = 0; i < NE; i++) v[i] += sp + q < d.nsplit ? x[q][i] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < NE; i++) {
+                const int u = u0 + 256 * i;
+                if (u < nel) {
+                    const int b3 = u / S, ss = u - b3 * S, m = ss / d.S3, c3 = ss - m * d.S3;
+                    td[m * PD + b3 * d.S3 + c3] = v[i];
+                }
+            }
+        }
+    };
+    for (int j = j0; j < j1; j++) {
+        __syncthreads();
+        if (d.nsplit > 4) load_tile(std::integral_constant<int, 8>(), std::integral_constant<int, 4>(), j);
+        else load_tile(std::integral_constant<int, 4>(), std::integral_constant<int, 8>(), j);
+        __syncthreads();
+        f32x16 db;
+#pragma unroll
+        for (int i = 0; i < 16; i++) db[i] = 0.f;
+        const float wj = t0[(32 * wr + cl) * d.KT + j];
+#pragma unroll 8
+        for (int k = 0; k < 64; k += 2) {
+            const int kk = k + hf;
+            const float b = t3[(32 * wr + cl) * kRP + kk] * wj, dm = td[cn * PD + kk];
+            const float a = ta[(32 * wr + cl) * kRP + kk], dn = td[kk * PD + cn];
+            da = __builtin_amdgcn_mfma_f32_32x32x2f32(b, dm, da, 0, 0, 0);
+            db = __builtin_amdgcn_mfma_f32_32x32x2f32(a, dn, db, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = 32 * wr + 8 * (i >> 2) + 4 * hf + (i & 3);
+            w3[i] += t0[r * d.KT + j] * db[i];
+            float v = t3[r * kRP + cn] * db[i];
+#pragma unroll
+            for (int x = 16; x >= 1; x >>= 1) v += __shfl_xor(v, x, 64);
+            if (cl == 0) q0[64 * wc + r] = v;
+        }
+        __syncthreads();
+        // tap partial [t1 t2][rank][tap]
+        if (tid < 64 && r0 + tid < d.R) P0[((int64_t)t12 * d.R + r0 + tid) * d.KT + j] = q0[tid] + q0[64 + tid];
+    }
+    // dW3 partial [(t1 t2) x tap group][rank][t3 s3]
+    if (cn < N) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = 32 * wr + 8 * (i >> 2) + 4 * hf + (i & 3);
+            if (r0 + r < d.R) P3[(((int64_t)t12 * d.NJ + jg) * d.R + r0 + r) * N + cn] = w3[i];
+        }
+    }
+    __syncthreads();
+    // dA tile to LDS as [s1 s2][rank] over the D tile
+#pragma unroll
+    for (int i = 0; i < 16; i++) td[cn * PD + 32 * wr + 8 * (i >> 2) + 4 * hf + (i & 3)] = da[i];
+    __syncthreads();
+    // dW1 partial [t2 x tap group][rank][t1][s1], dW2 partial [t1 x tap group][rank][t2][s2]
+    const int r = tid & 63;
+    if (r0 + r < d.R) {
+        const int64_t rr = r0 + r;
+        for (int x = tid >> 6; x < d.S1 + d.S2; x += 4) {
+            float v = 0.f;
+            if (x < d.S1) {
+                for (int s2 = 0; s2 < d.S2; s2++) v += td[(x * d.S2 + s2) * PD + r] * load(W2, (rr * d.T2 + a2) * d.S2 + s2);
+                P1[((((int64_t)a2 * d.NJ + jg) * d.R + rr) * d.T1 + a1) * d.S1 + x] = v;
+            } else {
+                const int s2 = x - d.S1;
+                for (int s1 = 0; s1 < d.S1; s1++) v += td[(s1 * d.S2 + s2) * PD + r] * load(W1, (rr * d.T1 + a1) * d.S1 + s1);
+                P2[((((int64_t)a1 * d.NJ + jg) * d.R + rr) * d.T2 + a2) * d.S2 + s2] = v;
+            }
+        }
+    }
+}
+
+template <typename D>
+D desc_of(const Launch& ln) {
+    D d;
+    std::memcpy(&d, ln.desc.data(), sizeof(d));
+    return d;
+}
+
+// dynamic LDS beyond 64 KB needs the attribute, once per kernel and device
+template <typename F>
+hipError_t allow_lds(F f, uint32_t bytes) {
+    if (bytes <= 65536) return hipSuccess;
+    static std::atomic<uint64_t> done{0};   // one mask per kernel instantiation (F differs per call site)
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 64 && ((done.load() >> dev) & 1)) return hipSuccess;
+    e = f();
+    if (e == hipSuccess && dev < 64) done.fetch_or(uint64_t(1) << dev);
+    return e;
+}
+
+}  // namespace
+
+template <typename T, int KS>
+static hipError_t conv_t(const Launch& ln, const DConvDesc& d, const void* x, const void* a, void* y, hipStream_t s) {
+    const dim3 g(ln.grid[0]), b(256);
+    constexpr int D = KS == 3 ? 3 : 5;
+#define CE_DCONV(KSP, MW, NW, MT, NT, D, NU)                                                                     \
+    do {                                                                                                         \
+        auto k = dconv<T, KS, KSP, MW, NW, MT, NT, D, NU>;                                                       \
+        hipError_t e = allow_lds([&] {                                                                           \
+            return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);  \
+        }, ln.lds);                                                                                              \
+        if (e != hipSuccess) return e;                                                                           \
+        hipLaunchKernelGGL(k, g, b, ln.lds, s, d, (const T*)x, (const uint4*)a, (T*)y);                          \
+        return hipGetLastError();                                                                                \
+    } while (0)
+    const int nu = (4 * d.t.slots + 255) / 256;
+    switch (d.cfg) {
+        case 0:
+            if (nu <= 4) CE_DCONV(1, 1, 4, 2, 2, D, 4);
+            CE_DCONV(1, 1, 4, 2, 2, D, 7);
+        case 1:
+            if (nu <= 4) CE_DCONV(1, 2, 2, 1, 2, 3 * D - 2 * (KS == 5) * D, 4);
+            CE_DCONV(1, 2, 2, 1, 2, 3 * D - 2 * (KS == 5) * D, 7);
+        case 2: CE_DCONV(4, 1, 1, 2, 2, D, 6);
+        default: return hipErrorInvalidValue;
+    }
+#undef CE_DCONV
+}
+
+hipError_t launch_dconv(const Launch& ln, const void* x, const void* a, void* y, hipStream_t s) {
+    const DConvDesc d = desc_of<DConvDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0] || (uint32_t)(8 * d.t.slots * kPitch * (d.cfg == 2 ? 4 : 1)) > ln.lds ||
+        (d.cfg == 2 && ln.lds < 65536) || d.t.KH != d.t.KW)
+        return hipErrorInvalidValue;
+    if (!((ln.kind >> kBitIn) & 1)) return hipErrorInvalidValue;
+    return d.t.KH == 3 ? conv_t<bf16_t, 3>(ln, d, x, a, y, s)
+         : d.t.KH == 5 ? conv_t<bf16_t, 5>(ln, d, x, a, y, s) : hipErrorInvalidValue;
+}
+
+template <typename T>
+static hipError_t wgrad_t(const Launch& ln, const DWgradDesc& d, const void* gr, const void* x, void* p, hipStream_t s) {
+    const dim3 g(ln.grid[0]);
+#define CE_DWGRAD(NS, NTG, TG)                                                                                   \
+    do {                                                                                                         \
+        auto k = dwgrad<T, NS, NTG, TG>;                                                                         \
+        if (ln.block[0] != 128 * NS * NTG) return hipErrorInvalidValue;                                          \
+        hipError_t e = allow_lds([&] {                                                                           \
+            return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);  \
+        }, ln.lds);                                                                                              \
+        if (e != hipSuccess) return e;                                                                           \
+        hipLaunchKernelGGL(k, g, dim3(128 * NS * NTG), ln.lds, s, d, (const T*)gr, (const T*)x, (float*)p);      \
+        return hipGetLastError();                                                                                \
+    } while (0)
+    switch (d.cfg) {
+        case 0: CE_DWGRAD(2, 2, 5);
+        case 1: CE_DWGRAD(1, 4, 7);
+        default: return hipErrorInvalidValue;
+    }
+#undef CE_DWGRAD
+}
+
+hipError_t launch_dwgrad(const Launch& ln, const void* g, const void* x, void* p, hipStream_t s) {
+    const DWgradDesc d = desc_of<DWgradDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0]) return hipErrorInvalidValue;
+    return ((ln.kind >> kBitIn) & 1) ? wgrad_t<bf16_t>(ln, d, g, x, p, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_rcp_merge(const Launch& ln, const void* const* ops, hipStream_t s) {
+    const DRcpDesc d = desc_of<DRcpDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0]) return hipErrorInvalidValue;
+    const dim3 g(ln.grid[0]), b(256);
+    if ((ln.kind >> kBitIn) & 1)
+        hipLaunchKernelGGL(rcp_merge<bf16_t>, g, b, ln.lds, s, d, (const bf16_t*)ops[0], (const bf16_t*)ops[1],
+                           (const bf16_t*)ops[2], (const bf16_t*)ops[3], (bf16_t*)const_cast<void*>(ops[4]));
+    else
+        hipLaunchKernelGGL(rcp_merge<float>, g, b, ln.lds, s, d, (const float*)ops[0], (const float*)ops[1],
+                           (const float*)ops[2], (const float*)ops[3], (float*)const_cast<void*>(ops[4]));
+    return hipGetLastError();
+}
+
+hipError_t launch_rcp_dfwd(const Launch& ln, const void* const* ops, void* y, hipStream_t s) {
+    const RcpDfwdDesc d = desc_of<RcpDfwdDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0] || d.lds_bytes != ln.lds || d.T2 * d.T3 > (d.S1 == 8 ? 64 : 32))
+        return hipErrorInvalidValue;
+#define CE_DFWD(kern, NTHR, NU)                                                                                  \
+    do {                                                                                                         \
+        auto k = kern;                                                                                           \
+        hipError_t e = allow_lds([&] {                                                                           \
+            return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);  \
+        }, ln.lds);                                                                                              \
+        if (e != hipSuccess) return e;                                                                           \
+        hipLaunchKernelGGL(k, dim3(ln.grid[0]), dim3(NTHR), ln.lds, s, d, (const bf16_t*)ops[0],                 \
+                           (const bf16_t*)ops[1], (const bf16_t*)ops[2], (const bf16_t*)ops[3],                  \
+                           (const bf16_t*)ops[4], (bf16_t*)y);                                                   \
+        return hipGetLastError();                                                                                \
+    } while (0)
+    if (d.t.KH == 3 && d.S1 == 8 && 2 * d.t.slots <= 64 * 4) CE_DFWD((rcp_dfwd_k<8, 3, 4>), 512, 4);
+    if (d.t.KH == 5 && d.S1 == 4 && 2 * d.t.slots <= 256 * 4) CE_DFWD((rcp_dfwd_p<4, 5, 4>), 256, 4);
+#undef CE_DFWD
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_rcp_fgrad(const Launch& ln, const void* const* ops, hipStream_t s) {
+    const DRcpDesc d = desc_of<DRcpDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0]) return hipErrorInvalidValue;
+    const dim3 g(ln.grid[0]), b(256);
+    float* p[4];
+    for (int i = 0; i < 4; i++) p[i] = (float*)const_cast<void*>(ops[5 + i]);
+    if ((ln.kind >> kBitIn) & 1)
+        hipLaunchKernelGGL(rcp_fgrad<bf16_t>, g, b, ln.lds, s, d, (const bf16_t*)ops[0], (const bf16_t*)ops[1],
+                           (const bf16_t*)ops[2], (const bf16_t*)ops[3], (const float*)ops[4], p[0], p[1], p[2], p[3]);
+    else
+        hipLaunchKernelGGL(rcp_fgrad<float>, g, b, ln.lds, s, d, (const float*)ops[0], (const float*)ops[1],
+                           (const float*)ops[2], (const float*)ops[3], (const float*)ops[4], p[0], p[1], p[2], p[3]);
+    return hipGetLastError();
+}
+
+}  // namespace ce

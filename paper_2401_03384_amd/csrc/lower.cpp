@@ -1486,4 +1486,121 @@ std::vector<Launch> lower_op(const ce_expr& e, const PairOp& op, unsigned flags,
     return out;
 }
 
+// ---- dense convolution tiles --------------------------------------------------
+namespace {
+
+constexpr int64_t kLdsMax = 160 * 1024;
+
+}  // namespace
+
+// Tile of at most `px` output pixels: whole images while they fit, else rows
+// of one image spread evenly; sets the staged extent.
+bool dense_tile(DTile& t, int64_t px) {
+    if (t.OW > px) return false;
+    const int64_t area = (int64_t)t.OH * t.OW;
+    if (area <= px) {
+        t.TH = t.OH;
+        t.NI = (int32_t)std::min<int64_t>(t.B, px / area);
+        t.NI = (t.B + (t.B + t.NI - 1) / t.NI - 1) / ((t.B + t.NI - 1) / t.NI);   // even groups
+    } else {
+        const int64_t rows = px / t.OW, n = (t.OH + rows - 1) / rows;
+        t.NI = 1;
+        t.TH = (int32_t)((t.OH + n - 1) / n);
+    }
+    t.nth = (t.OH + t.TH - 1) / t.TH;
+    t.HP = t.sth * (t.TH - 1) + t.KH;
+    t.WP = t.stw * (t.OW - 1) + t.KW;
+    const int64_t slots = (int64_t)t.NI * t.HP * t.WP, npt = (int64_t)((t.B + t.NI - 1) / t.NI) * t.nth;
+    if (slots > 65536 || npt > (1 << 28)) return false;
+    t.slots = (int32_t)slots;
+    t.npt = (int32_t)npt;
+    return true;
+}
+
+bool plan_dconv(DConvDesc& d, bool bf16, Launch& ln) {
+    const int64_t es = bf16 ? 2 : 4, CK = bf16 ? 32 : 16;
+    // rows, pixels and MFMAs a wavefront issues per tap of a chunk half
+    static const struct { int rows, px; double cost; } cfgs[] = {{64, 256, 4 / 0.7}, {64, 128, 2 / 0.55}, {64, 64, 1 / 0.4}};
+    if (d.t.KH != d.t.KW || (d.t.KH != 3 && d.t.KH != 5)) return false;
+    d.nch = (int32_t)((d.C + CK - 1) / CK);
+    double best = 0;
+    DConvDesc r = d;
+    bool found = false;
+    for (int c = 0; c < 3; c++) {
+        DConvDesc e = d;
+        if (!dense_tile(e.t, cfgs[c].px)) continue;
+        // cfg 2: a buffer pair a wavefront, and room for the four sums
+        const int64_t lds = c == 2 ? std::max<int64_t>(65536, 8 * (int64_t)e.t.slots * 80) : 2 * (int64_t)e.t.slots * 80;
+        if (lds > kLdsMax || es * e.t.NI * d.x_sb >= (1ll << 31)) continue;
+        e.cfg = c;
+        e.mblk = (d.M + cfgs[c].rows - 1) / cfgs[c].rows;
+        e.lds_bytes = (uint32_t)lds;
+        e.blocks = (int64_t)e.mblk * e.t.npt;
+        if (e.blocks > 0x7fffffff) continue;
+        const double cost = (double)((e.blocks + 255) / 256) * cfgs[c].cost;
+        if (found && cost >= best) continue;
+        best = cost;
+        r = e;
+        found = true;
+    }
+    if (!found) return false;
+    d = r;
+    ln = Launch();
+    ln.kind = K_DCONV | (bf16 ? (1 << kBitIn) | (1 << kBitAux) | (1 << kBitOut) : 0);
+    ln.grid[0] = (uint32_t)d.blocks;
+    ln.block[0] = 256;
+    ln.lds = d.lds_bytes;
+    ln.desc.resize(sizeof(d));
+    std::memcpy(ln.desc.data(), &d, sizeof(d));
+    static const char* tp[] = {"1, 1, 4, 2, 2", "1, 2, 2, 1, 2", "4, 1, 1, 2, 2"};
+    ln.kname = std::string("dconv<") + (bf16 ? "unsigned short, " : "float, ") + std::to_string(d.t.KH) + ", " + tp[d.cfg] + ">";
+    const double px = (double)d.t.B * d.t.OH * d.t.OW;
+    ln.alg_flops = 2.0 * px * d.M * d.C * d.t.KH * d.t.KW;
+    ln.alg_bytes = (double)es * (px * d.M + (double)d.t.B * d.t.H * d.t.W * d.C + (double)d.M * d.C * d.t.KH * d.t.KW);
+    return true;
+}
+
+bool plan_dwgrad(DWgradDesc& d, bool bf16, int64_t max_partial_bytes, Launch& ln) {
+    const int64_t es = bf16 ? 2 : 4, KT = (int64_t)d.t.KH * d.t.KW;
+    const int cfg = KT <= 10 ? 0 : KT <= 28 ? 1 : -1;
+    if (cfg < 0) return false;
+    const int64_t NS = cfg == 0 ? 2 : 1, pg = 64 * es + 16, px = 32 * NS * es + (NS == 1 && bf16 ? 32 : 16);
+    const int64_t zspan = (int64_t)(d.t.KH - 1);
+    bool found = false;
+    for (int64_t want : {256, 192, 128, 96, 64, 32}) {
+        if (!dense_tile(d.t, want)) continue;
+        d.PP = (int32_t)(((int64_t)d.t.NI * d.t.TH * d.t.OW + 15) / 16 * 16);
+        d.o_x = (uint32_t)(d.PP * pg);
+        d.o_tab = (uint32_t)(d.o_x + (d.t.slots + zspan * d.t.WP + d.t.KW) * px);
+        d.lds_bytes = (uint32_t)(d.o_tab + 4 * d.PP);
+        // at most four staging units a thread (512 threads) of either operand
+        const int64_t gu = 64 * es / 16 * d.PP, xu = 32 * NS * es / 16 * d.t.slots;
+        if (gu > 2048 || xu > 2048 || d.lds_bytes > kLdsMax || es * d.t.NI * std::max(d.x_sb, d.g_sb) >= (1ll << 31)) continue;
+        found = true;
+        break;
+    }
+    if (!found) return false;
+    d.cfg = cfg;
+    d.ntb = (d.T + 63) / 64;
+    d.nsb = (int32_t)((d.S + 32 * NS - 1) / (32 * NS));
+    const int64_t tiles = (int64_t)d.ntb * d.nsb, one = 4 * KT * d.T * d.S;
+    int64_t n = std::max<int64_t>(1, (256 + tiles / 2) / tiles);
+    n = std::min(n, std::max<int64_t>(1, max_partial_bytes / one));
+    d.nsplit = (int32_t)std::min<int64_t>(n, d.t.npt);
+    d.blocks = tiles * d.nsplit;
+    if (d.blocks > 0x7fffffff) return false;
+    ln = Launch();
+    ln.kind = K_DWGRAD | (bf16 ? (1 << kBitIn) | (1 << kBitAux) : 0);
+    ln.grid[0] = (uint32_t)d.blocks;
+    ln.block[0] = 512;
+    ln.lds = d.lds_bytes;
+    ln.desc.resize(sizeof(d));
+    std::memcpy(ln.desc.data(), &d, sizeof(d));
+    ln.kname = std::string("dwgrad<") + (bf16 ? "unsigned short, " : "float, ") + (cfg == 0 ? "2, 2, 5>" : "1, 4, 7>");
+    const double pxs = (double)d.t.B * d.t.OH * d.t.OW;
+    ln.alg_flops = 2.0 * pxs * d.T * d.S * KT;
+    ln.alg_bytes = es * (pxs * d.T + (double)d.t.B * d.t.H * d.t.W * d.S) + (double)d.nsplit * one;
+    return true;
+}
+
 }  // namespace ce

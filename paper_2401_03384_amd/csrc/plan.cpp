@@ -840,10 +840,23 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
             fs.t = s;
             for (auto& l : lower_op(E, fops[s], flags, fs)) p->fwd.push_back(l);
         }
+        // the merged-kernel form of a chain holds a tensor the plan's caps did
+        // not weigh, and keeps no intermediates a caller asked to keep
+        const bool dense_ok = lim.max_elements == ~uint64_t(0) && lim.max_step_cost == ~uint64_t(0) &&
+                              lim.save_budget == 0 && !(flags & CE_FLAG_SAVE_INTERMEDIATES);
+        Launch rcp_chain;
         if (!(flags & CE_FLAG_GENERIC_ONLY) && !(flags & CE_FLAG_NO_FUSION)) {
             fuse_launches(p->fwd, false);
             Launch rf;
-            if (fuse_rcp_forward(*p, rf)) p->fwd.assign(1, rf);
+            if (fuse_rcp_forward(*p, rf)) {
+                rcp_chain = rf;
+                if (dense_ok) dense_rcp_onelaunch(*p, rf);
+                p->fwd.assign(1, rf);
+            } else if (dense_ok) {
+                std::vector<Launch> v;
+                fs.t = 0;
+                if (dense_rcp_forward(*p, fs, v)) p->fwd.swap(v);
+            }
         }
         drop_unused(items, p->fwd);
         // Checkpointing (Section 3.3): the intermediates the forward writes
@@ -961,17 +974,20 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
                 fused_bwd = true;
             }
         }
-        if (!(flags & CE_FLAG_GENERIC_ONLY) && !(flags & CE_FLAG_NO_FUSION) && p->fwd.size() == 1 &&
-            (p->fwd[0].kind & 0xff) == K_RCP_FWD) {
-            std::vector<WsItem> fitems;
-            ItemScratch fsc;
-            fsc.items = &fitems;
-            fsc.next = SCRATCH_ID;
-            std::vector<Launch> v;
-            if (fuse_rcp_backward(p->fwd[0], *p, fsc, v)) {
-                p->bwd.swap(v);
-                bitems.swap(fitems);
-                fused_bwd = true;
+        const bool chain = (rcp_chain.kind & 0xff) == K_RCP_FWD;   // a fused reshaped-CP forward
+        if (!(flags & CE_FLAG_GENERIC_ONLY) && !(flags & CE_FLAG_NO_FUSION) && !fused_bwd && (chain || dense_ok)) {
+            for (int form = 0; form < 2 && !fused_bwd; form++) {   // merged kernel, then the chain's own
+                std::vector<WsItem> fitems;
+                ItemScratch fsc;
+                fsc.items = &fitems;
+                fsc.next = SCRATCH_ID;
+                std::vector<Launch> v;
+                if (form == 0 ? dense_ok && dense_rcp_backward(*p, chain, fsc, v)
+                              : chain && fuse_rcp_backward(rcp_chain, *p, fsc, v)) {
+                    p->bwd.swap(v);
+                    bitems.swap(fitems);
+                    fused_bwd = true;
+                }
             }
         }
         ItemScratch bs;

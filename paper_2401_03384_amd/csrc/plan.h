@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "desc.h"
+#include "desc_dense.h"
 #include "expr.h"
 
 namespace ce {
@@ -163,11 +164,30 @@ bool fuse_rcp_forward(const ce_plan& p, Launch& out);
 // factor gradients per workgroup), then their ordered sums.
 bool fuse_rcp_backward(const Launch& f, const ce_plan& p, ScratchAlloc& scratch, std::vector<Launch>& out);
 
+// The dense-kernel form of a reshaped-CP plan (merged kernel, then one
+// convolution): forward launches with the packed kernel in scratch, and the
+// backward (input gradient through the merged kernel, the kernel's gradient,
+// the factors' gradients).  False when the sizes are not covered or the
+// chain's own kernels are cheaper.
+// dense_rcp_onelaunch turns the fused forward launch `f` into the one that
+// merges the kernel on chip (no scratch).
+bool dense_rcp_onelaunch(const ce_plan& p, Launch& f);
+bool dense_rcp_forward(const ce_plan& p, ScratchAlloc& scratch, std::vector<Launch>& out);
+// chain: the alternative is the fused chain backward.
+bool dense_rcp_backward(const ce_plan& p, bool chain, ScratchAlloc& scratch, std::vector<Launch>& out);
+
 // A contraction step `prod` and the convolution step `cons` that consumes its
 // result as one fused launch (K_TT_FWD), when their labels and layouts fit
 // the fused kernel; `out` reads the producer's operands and the consumer's
 // other operand and writes the consumer's result.
 bool fuse_tt_forward(const PairOp& prod, const PairOp& cons, Launch& out);
+
+// Dense convolution and kernel-gradient launches (desc_dense.h): fill the
+// tile, the split and the launch shape of a descriptor whose problem sizes,
+// strides and taps are set.  False when no tile fits.
+bool dense_tile(DTile& t, int64_t px);
+bool plan_dconv(DConvDesc& d, bool bf16, Launch& ln);
+bool plan_dwgrad(DWgradDesc& d, bool bf16, int64_t max_partial_bytes, Launch& ln);
 
 // Lowering of one pairwise op to launches: a specialised kernel when the
 // op's label structure fits one (unless CE_FLAG_GENERIC_ONLY), else generic.

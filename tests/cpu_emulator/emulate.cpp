@@ -1442,6 +1442,222 @@ bool run_cred(const Launch& ln, Ctx& c) {
     return true;
 }
 
+// ---- dense-kernel launches (desc_dense.h) ------------------------------------
+// Tile geometry of the dense kernels: every staged slot a tap reads lies in
+// the tile, and the pixel tiles cover every output position once.
+bool check_tile(const DTile& t, int64_t px, const Launch& ln, Ctx& c) {
+    REQ(t.NI >= 1 && t.TH >= 1 && t.TH <= t.OH && (t.NI == 1 || t.TH == t.OH) && t.nth == (t.OH + t.TH - 1) / t.TH &&
+        t.npt == (t.B + t.NI - 1) / t.NI * t.nth && (int64_t)t.NI * t.TH * t.OW <= px &&
+        t.HP >= t.sth * (t.TH - 1) + std::abs(t.zhs) * (t.KH - 1) + 1 &&
+        t.WP >= t.stw * (t.OW - 1) + std::abs(t.zws) * (t.KW - 1) + 1 && t.slots == t.NI * t.HP * t.WP, "dense tile");
+    return true;
+}
+
+// value of plane `b`, channel ch at the input position of output (r, cc), tap (i, j)
+float tap_value(const Buf& X, int dt, const DTile& t, int64_t o, int r, int cc, int i, int j, bool& ok) {
+    const int hh = t.sth * r + t.zh0 + t.zhs * i, ww = t.stw * cc + t.zw0 + t.zws * j;
+    if (hh < 0 || hh >= t.H || ww < 0 || ww >= t.W) return 0.f;
+    return ld(X, dt, o + (int64_t)hh * t.W + ww, ok);
+}
+
+bool run_dconv(const Launch& ln, Ctx& c) {
+    DConvDesc d = desc_of<DConvDesc>(ln);
+    const DTile& t = d.t;
+    const int bf = (ln.kind >> kBitIn) & 1, CK = bf ? 32 : 16, EPU = bf ? 8 : 4;
+    const int rows = 64, pxs[] = {256, 128, 64};
+    REQ(d.cfg >= 0 && d.cfg < 3 && check_tile(t, pxs[d.cfg], ln, c) && d.nch == (d.C + CK - 1) / CK &&
+        d.mblk == (d.M + rows - 1) / rows && d.blocks == (int64_t)d.mblk * t.npt && ln.grid[0] == d.blocks &&
+        ln.block[0] == 256 && ln.lds == d.lds_bytes && (int64_t)ln.lds >= (d.cfg == 2 ? 8 : 2) * 80ll * t.slots &&
+        ln.lds <= 160 * 1024, "dense convolution layout");
+    bool ok = true, o1, o2, o3;
+    Buf X = resolve(ln.a, c, 0, o1), A = resolve(ln.b, c, 0, o2), Y = resolve(ln.c, c, 0, o3);
+    REQ(o1 && o2 && o3, "unresolved buffer");
+    const int KT = t.KH * t.KW;
+    for (int64_t pt = 0; pt < t.npt; pt++) {
+        const int ti = (int)(pt / t.nth), h0 = (int)(pt % t.nth) * t.TH, b0 = ti * t.NI;
+        for (int n = 0; n < t.NI * t.TH * t.OW; n++) {
+            const int img = n / (t.TH * t.OW), r = h0 + n / t.OW % t.TH, cc = n % t.OW, b = b0 + img;
+            if (b >= t.B || r >= t.OH) continue;
+            for (int m = 0; m < d.M; m++) {
+                double acc = 0;
+                for (int ch = 0; ch < d.C; ch++)
+                    for (int j = 0; j < KT; j++) {
+                        const int u = ch % CK / EPU;
+                        const int64_t o = ((((int64_t)(m / 32) * d.nch + ch / CK) * KT + j) * 128 + (u >> 1) * 64 + (u & 1) * 32 + m % 32) * EPU + ch % EPU;
+                        acc += (double)ld(A, bf, o, ok) * tap_value(X, bf, t, b * d.x_sb + ch * d.x_sc, r, cc, j / t.KW, j % t.KW, ok);
+                    }
+                st(Y, bf, b * d.y_sb + m * d.y_sm + r * d.y_sh + cc * d.y_sw, (float)acc, ok);
+            }
+        }
+    }
+    REQ(ok, "out-of-bounds (dense convolution)");
+    return true;
+}
+
+bool run_dwgrad(const Launch& ln, Ctx& c) {
+    DWgradDesc d = desc_of<DWgradDesc>(ln);
+    const DTile& t = d.t;
+    const int bf = (ln.kind >> kBitIn) & 1, es = bf ? 2 : 4, KT = t.KH * t.KW, NS = d.cfg == 0 ? 2 : 1;
+    const int64_t pg = 64 * es + 16, px = 32 * NS * es + (NS == 1 && bf ? 32 : 16);
+    REQ((d.cfg == 0 ? KT <= 10 : d.cfg == 1 && KT <= 28) && check_tile(t, d.PP, ln, c) && d.PP % 16 == 0 && d.PP <= 512 &&
+        64 * es / 16 * d.PP <= 2048 && 32 * NS * es / 16 * t.slots <= 2048 && d.o_x == d.PP * pg &&
+        d.o_tab == d.o_x + (t.slots + (t.KH - 1) * t.WP + t.KW) * px && d.lds_bytes == d.o_tab + 4 * d.PP &&
+        ln.lds == d.lds_bytes && ln.lds <= 160 * 1024 && d.ntb == (d.T + 63) / 64 && d.nsb == (d.S + 32 * NS - 1) / (32 * NS) &&
+        d.nsplit >= 1 && d.nsplit <= t.npt && d.blocks == (int64_t)d.ntb * d.nsb * d.nsplit && ln.grid[0] == d.blocks &&
+        ln.block[0] == 512, "kernel-gradient layout");
+    bool ok = true, o1, o2, o3;
+    Buf G = resolve(ln.a, c, 0, o1), X = resolve(ln.b, c, 0, o2), P = resolve(ln.d, c, 0, o3);
+    REQ(o1 && o2 && o3, "unresolved buffer");
+    for (int sp = 0; sp < d.nsplit; sp++)
+        for (int j = 0; j < KT; j++)
+            for (int tt = 0; tt < d.T; tt++)
+                for (int ss = 0; ss < d.S; ss++) {
+                    double acc = 0;
+                    for (int64_t pt = (int64_t)t.npt * sp / d.nsplit; pt < (int64_t)t.npt * (sp + 1) / d.nsplit; pt++) {
+                        const int b0 = (int)(pt / t.nth) * t.NI, h0 = (int)(pt % t.nth) * t.TH;
+                        for (int b = b0; b < std::min(t.B, b0 + t.NI); b++)
+                            for (int r = h0; r < std::min(t.OH, h0 + t.TH); r++)
+                                for (int cc = 0; cc < t.OW; cc++)
+                                    acc += (double)ld(G, bf, b * d.g_sb + tt * d.g_sc + (int64_t)r * t.OW + cc, ok) *
+                                           tap_value(X, bf, t, b * d.x_sb + ss * d.x_sc, r, cc, j / t.KW, j % t.KW, ok);
+                    }
+                    st(P, 0, (((int64_t)sp * KT + j) * d.T + tt) * d.S + ss, (float)acc, ok);
+                }
+    REQ(ok, "out-of-bounds (kernel gradient)");
+    return true;
+}
+
+// W[t][s][j] of a reshaped-CP layer from its factors, ranks r0 .. r1
+struct RcpFactors {
+    Buf W1, W2, W3, W0;
+    int bf;
+    double at(const DRcpDesc& d, int tt, int ss, int j, int r, bool& ok) const {
+        const int a1 = tt / (d.T2 * d.T3), a2 = tt / d.T3 % d.T2, a3 = tt % d.T3;
+        const int c1 = ss / (d.S2 * d.S3), c2 = ss / d.S3 % d.S2, c3 = ss % d.S3;
+        return (double)ld(W1, bf, ((int64_t)r * d.T1 + a1) * d.S1 + c1, ok) * ld(W2, bf, ((int64_t)r * d.T2 + a2) * d.S2 + c2, ok) *
+               ld(W3, bf, ((int64_t)r * d.T3 + a3) * d.S3 + c3, ok) * ld(W0, bf, (int64_t)r * d.KT + j, ok);
+    }
+};
+
+bool rcp_factors(const Launch& ln, Ctx& c, RcpFactors& f) {
+    bool o[4];
+    f.W1 = resolve(ln.extra[0], c, 0, o[0]);
+    f.W2 = resolve(ln.extra[1], c, 0, o[1]);
+    f.W3 = resolve(ln.extra[2], c, 0, o[2]);
+    f.W0 = resolve(ln.extra[3], c, 0, o[3]);
+    f.bf = (ln.kind >> kBitIn) & 1;
+    REQ(o[0] && o[1] && o[2] && o[3], "unresolved buffer");
+    return true;
+}
+
+bool run_rcp_merge(const Launch& ln, Ctx& c) {
+    DRcpDesc d = desc_of<DRcpDesc>(ln);
+    RcpFactors f;
+    if (!rcp_factors(ln, c, f)) return false;
+    bool ok = true, o1;
+    Buf O = resolve(ln.extra[4], c, 0, o1);
+    const int EPU = f.bf ? 8 : 4, T = d.T1 * d.T2 * d.T3, S = d.S1 * d.S2 * d.S3;
+    REQ(o1 && d.S1 * d.S2 <= 64 && d.T3 * d.S3 <= 64 && d.KT <= 28 && d.jper * (d.NJ - 1) < d.KT && d.jper * d.NJ >= d.KT &&
+        d.nrc == (d.R + 63) / 64 && d.blocks == (int64_t)d.T1 * d.T2 * d.NJ && ln.grid[0] == d.blocks &&
+        ln.block[0] == 256 && ln.lds >= 4u * (128 * 68 + 64 * d.KT) && ln.lds <= 65536 &&
+        d.nch == ((d.transposed ? T : S) + 4 * EPU - 1) / (4 * EPU), "merged kernel layout");
+    for (int tt = 0; tt < T; tt++)
+        for (int ss = 0; ss < S; ss++)
+            for (int j = 0; j < d.KT; j++) {
+                double acc = 0;
+                for (int r = 0; r < d.R; r++) acc += f.at(d, tt, ss, j, r, ok);
+                const int row = d.transposed ? ss : tt, ch = d.transposed ? tt : ss, u = ch / EPU & 3;
+                const int64_t o = (((int64_t)(row / 32) * d.nch + ch / (4 * EPU)) * d.KT + j) * 128 + (u >> 1) * 64 + (u & 1) * 32 + row % 32;
+                st(O, f.bf, o * EPU + ch % EPU, (float)acc, ok);
+            }
+    REQ(ok, "out-of-bounds (merged kernel)");
+    return true;
+}
+
+bool run_rcp_fgrad(const Launch& ln, Ctx& c) {
+    DRcpDesc d = desc_of<DRcpDesc>(ln);
+    RcpFactors f;
+    if (!rcp_factors(ln, c, f)) return false;
+    bool ok = true, o[5];
+    Buf D = resolve(ln.extra[4], c, 0, o[0]), P[4];
+    for (int i = 0; i < 4; i++) P[i] = resolve(ln.extra[5 + i], c, 0, o[1 + i]);
+    REQ(o[0] && o[1] && o[2] && o[3] && o[4] && d.S1 * d.S2 <= 64 && d.T3 * d.S3 <= 64 && d.KT <= 28 &&
+        d.jper * (d.NJ - 1) < d.KT && d.jper * d.NJ >= d.KT && d.nrc == (d.R + 63) / 64 &&
+        d.blocks == (int64_t)d.T1 * d.T2 * d.NJ * d.nrc && ln.grid[0] == d.blocks && ln.block[0] == 256 &&
+        ln.lds >= 4u * (128 * 68 + 64 * 65 + 64 * d.KT + 128) && ln.lds <= 65536, "factor gradient layout");
+    const int S = d.S1 * d.S2 * d.S3, T = d.T1 * d.T2 * d.T3, N3 = d.T3 * d.S3;
+    for (int a1 = 0; a1 < d.T1; a1++)
+        for (int a2 = 0; a2 < d.T2; a2++)
+            for (int jg = 0; jg < d.NJ; jg++)
+                for (int r = 0; r < d.R; r++) {
+                    std::vector<double> g1(d.S1), g2(d.S2), g3(N3), g0(d.KT);
+                    for (int j = jg * d.jper; j < std::min(d.KT, (jg + 1) * d.jper); j++)
+                        for (int a3 = 0; a3 < d.T3; a3++)
+                            for (int ss = 0; ss < S; ss++) {
+                                const int tt = (a1 * d.T2 + a2) * d.T3 + a3, c1 = ss / (d.S2 * d.S3), c2 = ss / d.S3 % d.S2, c3 = ss % d.S3;
+                                double v = 0;
+                                for (int sp = 0; sp < d.nsplit; sp++) v += ld(D, 0, (((int64_t)sp * d.KT + j) * T + tt) * S + ss, ok);
+                                const double w1 = ld(f.W1, f.bf, ((int64_t)r * d.T1 + a1) * d.S1 + c1, ok), w2 = ld(f.W2, f.bf, ((int64_t)r * d.T2 + a2) * d.S2 + c2, ok);
+                                const double w3 = ld(f.W3, f.bf, ((int64_t)r * d.T3 + a3) * d.S3 + c3, ok), w0 = ld(f.W0, f.bf, (int64_t)r * d.KT + j, ok);
+                                g1[c1] += v * w2 * w3 * w0;
+                                g2[c2] += v * w1 * w3 * w0;
+                                g3[a3 * d.S3 + c3] += v * w1 * w2 * w0;
+                                g0[j] += v * w1 * w2 * w3;
+                            }
+                    const int64_t t12 = a1 * d.T2 + a2;
+                    for (int x = 0; x < d.S1; x++) st(P[0], 0, ((((int64_t)a2 * d.NJ + jg) * d.R + r) * d.T1 + a1) * d.S1 + x, (float)g1[x], ok);
+                    for (int x = 0; x < d.S2; x++) st(P[1], 0, ((((int64_t)a1 * d.NJ + jg) * d.R + r) * d.T2 + a2) * d.S2 + x, (float)g2[x], ok);
+                    for (int x = 0; x < N3; x++) st(P[2], 0, ((t12 * d.NJ + jg) * d.R + r) * N3 + x, (float)g3[x], ok);
+                    for (int j = jg * d.jper; j < std::min(d.KT, (jg + 1) * d.jper); j++) st(P[3], 0, (t12 * d.R + r) * d.KT + j, (float)g0[j], ok);
+                }
+    REQ(ok, "out-of-bounds (factor gradients)");
+    return true;
+}
+
+// the one-launch forward: its tile, tables and LDS layout, then the layer by definition
+bool run_rcp_dfwd(const Launch& ln, Ctx& c) {
+    RcpDfwdDesc d = desc_of<RcpDfwdDesc>(ln);
+    const DTile& t = d.t;
+    const bool k3 = t.KH == 3;
+    const int KT = t.KH * t.KW, S23 = d.S2 * d.S3, PR = 16 * d.RK + 4, tiles = (KT + 32 / d.S1 - 1) / (32 / d.S1);
+    REQ(((k3 && d.S1 == 8 && d.T2 * d.T3 == 64 && 2 * t.slots <= 256) || (t.KH == 5 && d.S1 == 4 && d.T2 * d.T3 == 32 && 2 * t.slots <= 1024)) &&
+        check_tile(t, k3 ? 64 : 256, ln, c) && t.sth == 1 && t.stw == 1 && d.RK == (d.R + 15) / 16 && d.nch * (16 / d.S1) == S23 &&
+        d.o_w2 >= d.o_f + 1024u * tiles * d.RK && d.o_w3 >= d.o_w2 + 4u * d.T2 * d.S2 * PR && d.o_w >= d.o_w3 + 4u * d.T3 * d.S3 * PR &&
+        d.o_x >= d.o_w + (k3 ? 0u : 2048u * KT) && d.lds_bytes >= d.o_x + (k3 ? 8u : 2u) * 48 * t.slots && (!k3 || d.lds_bytes >= d.o_x + 65536) &&
+        d.lds_bytes <= 160 * 1024 && ln.lds == d.lds_bytes && d.blocks == (int64_t)d.T1 * t.npt && ln.grid[0] == d.blocks &&
+        ln.block[0] == (k3 ? 512u : 256u), "one-launch reshaped-CP layout");
+    bool ok = true, o[6];
+    Buf X = resolve(ln.a, c, 0, o[0]), Y = resolve(ln.c, c, 0, o[5]);
+    RcpFactors f;
+    f.bf = 1;
+    f.W1 = resolve(ln.b, c, 0, o[1]);
+    f.W2 = resolve(ln.extra[0], c, 0, o[2]);
+    f.W3 = resolve(ln.extra[1], c, 0, o[3]);
+    f.W0 = resolve(ln.extra[2], c, 0, o[4]);
+    REQ(o[0] && o[1] && o[2] && o[3] && o[4] && o[5], "unresolved buffer");
+    DRcpDesc q;
+    std::memset(&q, 0, sizeof(q));
+    q.R = d.R; q.T1 = d.T1; q.T2 = d.T2; q.T3 = d.T3; q.S1 = d.S1; q.S2 = d.S2; q.S3 = d.S3; q.KT = KT;
+    const int T = d.T1 * d.T2 * d.T3, S = d.S1 * S23, HW = t.H * t.W;
+    std::vector<double> acc((size_t)t.B * HW);
+    for (int tt = 0; tt < T; tt++) {
+        std::fill(acc.begin(), acc.end(), 0.0);
+        for (int ss = 0; ss < S; ss++)
+            for (int j = 0; j < KT; j++) {
+                double w = 0;
+                for (int r = 0; r < d.R; r++) w += f.at(q, tt, ss, j, r, ok);
+                for (int b = 0; b < t.B; b++)
+                    for (int r = 0; r < t.H; r++)
+                        for (int cc = 0; cc < t.W; cc++)
+                            acc[(size_t)b * HW + r * t.W + cc] += w * tap_value(X, 1, t, ((int64_t)b * S + ss) * HW, r, cc, j / t.KW, j % t.KW, ok);
+            }
+        for (int b = 0; b < t.B; b++)
+            for (int p = 0; p < HW; p++) st(Y, 1, ((int64_t)b * T + tt) * HW + p, (float)acc[(size_t)b * HW + p], ok);
+    }
+    REQ(ok, "out-of-bounds (one-launch reshaped CP)");
+    return true;
+}
+
 // K_WGCONV (the K_CREDW partials on fp32 MFMA tiles): the launcher's
 // descriptor checks; every Z / O / partial index and every LDS word the
 // kernel's lanes touch, walked block by block with its own offset
@@ -1785,6 +2001,11 @@ int emul_run(const char* spec, int n, const int* ranks, const int64_t* const* di
                     : v == K_CCONV ? run_cconv(ln, c)
                     : v == K_WGCONV ? run_wgconv(ln, c)
                     : v == K_GPAIR ? run_gpair(ln, c)
+                    : v == K_DCONV ? run_dconv(ln, c)
+                    : v == K_DWGRAD ? run_dwgrad(ln, c)
+                    : v == K_RCP_MERGE ? run_rcp_merge(ln, c)
+                    : v == K_RCP_FGRAD ? run_rcp_fgrad(ln, c)
+                    : v == K_RCP_DFWD ? run_rcp_dfwd(ln, c)
                     : v == K_TT_FWD || v == K_TT_PREP ? run_tt_fwd(ln, c)
                     : (v == K_THINW || v == K_THINW_REDUCE) ? run_thinw(ln, c)
                     : (c.err = "unknown launch kind", false);

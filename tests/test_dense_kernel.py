@@ -1,0 +1,80 @@
+"""Layers evaluated through their merged dense kernel (reshaped CP in bf16):
+the merge, the convolution, the kernel's gradient and the factor gradients,
+at sizes off their tiles; on the CPU through the emulated launch lists, on the
+GPU against the dense oracle."""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from test_emulated_plans import _rel, _run, emul  # noqa: F401  (the emulator fixture)
+
+# (batch, s modes, t modes, height, width, rank, taps)
+CASES = {
+    # partial channel chunk (90 of 96), 30-row modes, odd plane, rank off 16
+    "odd_modes": (3, (3, 5, 6), (2, 4, 8), 13, 9, 37, 3),
+    # two chunks of 64 ranks, several row tiles a plane
+    "rank70": (2, (2, 4, 8), (8, 8, 8), 20, 56, 70, 3),
+    # 5x5 taps, one image group and a partial one
+    "k5_groups": (7, (4, 4, 4), (4, 8, 8), 7, 7, 16, 5),
+    # the one-launch forwards: an even rank off 16 steps, partial tiles, t1 of 3
+    "one_k3": (3, (8, 8, 8), (3, 8, 8), 9, 5, 22, 3),
+    "one_k5": (2, (4, 4, 8), (3, 4, 8), 23, 26, 18, 5),
+    "one_k5_r70": (1, (4, 4, 8), (2, 4, 8), 6, 60, 70, 5),
+}
+SMALL = {
+    "odd_modes": (2, (3, 5, 6), (2, 4, 2), 5, 7, 20, 3),
+    "k5_groups": (3, (2, 4, 4), (2, 2, 4), 7, 7, 8, 5),
+    "one_k3": (1, (8, 8, 8), (1, 8, 8), 4, 5, 18, 3),
+    "one_k5": (1, (4, 4, 8), (2, 4, 8), 6, 7, 10, 5),
+    "rank70": (1, (2, 2, 2), (2, 2, 3), 4, 6, 70, 3),
+}
+
+
+def _layer(name, case):
+    b, ss, ts, h, w, r, k = case
+    return W.rcp_layer(name, b, ss, ts, h, w, r, k, "bf16", 91)
+
+
+@pytest.mark.parametrize("name", sorted(SMALL))
+def test_emulated(emul, name):  # noqa: F811
+    w = _layer(name, SMALL[name])
+    ins, dy = W.make_inputs(w)
+    e = O.bind(O.parse(w.spec), w.shapes)
+    y = _run(emul, w.spec, w.shapes, True, 0, ins, out_shape=w.out_shape, generic=0)
+    assert _rel(y, O.eval_dense(e, ins)) <= 1e-2
+    g = _run(emul, w.spec, w.shapes, True, 1, ins, dy=dy, generic=0)
+    for a, b in zip(g, O.grads_dense(e, ins, dy)):
+        assert _rel(a, b) <= 1e-2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_gpu(name):
+    """Y and dX are rounded once themselves and once or twice in the merged
+    kernel, each rounding uniform within half a bf16 ulp: at most
+    sqrt(3) * 2^-9 / sqrt(3) = 2^-9 of a value's binade in rms, 4e-3 as a
+    bound.  The factor gradients are fp32 sums of exact products throughout:
+    1e-5, the fp32 bar."""
+    import torch
+    import paper_2401_03384_amd as P
+    w = _layer(name, CASES[name])
+    ins, dy = W.make_inputs(w)
+    plan = P.Plan(w.spec, w.shapes, w.dtype)
+    text = plan.describe()
+    assert "dwgrad<" in text and "rcp_fgrad<" in text and "dconv<" in text, text
+    assert ("rcp_dfwd" in text) == name.startswith("one_"), text
+    dev = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16().cuda()  # noqa: E731
+    xs, d = [dev(a) for a in ins], dev(dy)
+    y = plan.forward(xs)
+    g = plan.backward(xs, d)
+    e = O.bind(O.parse(w.spec), w.shapes)
+    host = lambda t: t.double().cpu().numpy()  # noqa: E731
+    assert _rel(host(y), O.eval_dense(e, ins)) <= 4e-3
+    ref = O.grads_dense(e, ins, dy)
+    assert _rel(host(g[0]), ref[0]) <= 4e-3
+    for a, b in zip(g[1:], ref[1:]):
+        assert _rel(host(a), b) <= 1e-5
+    # the same values again, and a gradient alone as among the others
+    part = plan.backward(xs, d, needs=[False, True, False, False, True])
+    assert torch.equal(part[1], g[1]) and torch.equal(part[4], g[4]) and part[0] is None
