@@ -73,6 +73,7 @@ enum KernelKind : int32_t {
     K_RCP_MERGE = 43,       // merged, packed kernel of a reshaped-CP layer (DRcpDesc)
     K_RCP_DFWD = 45,        // reshaped-CP forward merging its kernel on chip (RcpDfwdDesc)
     K_RCP_FGRAD = 44,       // its factor gradients' partials from the kernel's gradient (DRcpDesc)
+    K_FILL = 46,            // zeros over a dense buffer (int64_t: its bytes)
 };
 
 // Launch kind = variant | element-type bits (1 = bfloat16, 0 = float32).

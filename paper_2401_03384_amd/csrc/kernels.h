@@ -14,6 +14,9 @@ hipError_t launch_generic(const Launch& ln, const void* a, const void* b, void* 
 hipError_t launch_fast(const Launch& ln, const void* a, const void* b, void* c, void* d,
                        hipStream_t s);
 
+// Zeros over a dense buffer (K_FILL, int64_t bytes).
+hipError_t launch_fill(const Launch& ln, void* c, hipStream_t s);
+
 // Up to four ordered partial sums (K_REDUCE_MULTI, MultiReduceDesc): parts[j]
 // the fp32 partials, outs[j] the fp32 output (null: skipped).
 hipError_t launch_reduce_multi(const Launch& ln, const void* const* parts, void* const* outs, hipStream_t s);

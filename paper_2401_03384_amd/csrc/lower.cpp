@@ -1387,6 +1387,15 @@ bool try_gpair_ops(const PairOp& gl, const PairOp& gr, ScratchAlloc& scratch, st
         if (N >= ((int64_t)1 << 31) || fnumel >= ((int64_t)1 << 31) || d.blocks * fnumel > ((int64_t)1 << 28) ||
             d.gext * 4 >= ((int64_t)1 << 31) || d.aext * 4 >= ((int64_t)1 << 31) || sG1 < 0 || sG2 < 0 || sAm < 0)
             continue;
+        // A block walks its tiles and chunks one after another, 1.6 us each on a
+        // full chip and 2.4 us alone; two separate launches read dC twice at
+        // about 2.5 TB/s and multiply at about 40 TFLOP/s, after some 25 us (40
+        // for long rows, on the general contraction) of launches.  Few samples leave the
+        // fused kernel with few blocks (X[24,48,37,29], rank 20: 47 + 6 us
+        // against 10 + 11 + 6 us; one 56x56 sample: 115 against 24 us).
+        const double serial = (double)cdiv(d.blocks, 256) * d.gper * d.ntiles * d.nkc * (d.blocks < 256 ? 2.4 : 1.6);
+        const double moved = 2 * tensor_bytes(Gt) + 2 * tensor_bytes(At);
+        if (serial > (d.nkc == 1 ? 25.0 : 40.0) + moved / 2.5e6 + 4.0 * (double)gl.macs / 40e6) continue;
         const BufRef part = scratch.alloc((size_t)(d.blocks * fnumel * 4));
         Launch ln;
         ln.kind = K_GPAIR | dt_bits(DT_F32, DT_F32, DT_F32);
@@ -1454,6 +1463,30 @@ std::vector<Launch> lower_op(const ce_expr& e, const PairOp& op, unsigned flags,
     bool circular = false;   // circular maps run on the generic kernel only
     for (const ConvMap& cm : op.convs)
         if (cm.modL || cm.modR) circular = true;
+    if (op.generic_only && !(flags & CE_FLAG_GENERIC_ONLY)) {
+        // zeros over the whole (dense) result: 16 bytes a thread
+        const int64_t es = op.C.dtype == DT_BF16 ? 2 : 4, n = op.C.numel() * es;
+        int64_t expect = 1;
+        bool dense = n >= 1 && n <= ((int64_t)1 << 38);
+        for (int k = (int)op.C.dims.size() - 1; k >= 0; --k) {
+            dense = dense && (op.C.strides[k] == expect || op.C.dims[k] == 1);
+            expect *= op.C.dims[k];
+        }
+        if (dense) {
+            Launch ln;
+            ln.kind = K_FILL;
+            ln.c = op.C.buf;
+            ln.grid[0] = (uint32_t)cdiv(n, 16 * 256);
+            ln.block[0] = 256;
+            set_desc(ln, n);
+            ln.kname = "fill_zero";
+            ln.need = op.need;
+            ln.what = op.what;
+            ln.alg_bytes = (double)n;
+            out.push_back(ln);
+            return out;
+        }
+    }
     bool fast = !(flags & CE_FLAG_GENERIC_ONLY) && !op.generic_only && !circular &&
                 (try_gemm(op, out) || try_wgrad(op, scratch, out) || try_dw(op, scratch, out) ||
                  try_cred(op, scratch, out) || try_cconv(op, out) || try_thinw(op, scratch, out) ||

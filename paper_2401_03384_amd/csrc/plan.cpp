@@ -379,6 +379,7 @@ struct Builder {
         int64_t nph = 1;
         for (int k : idx) nph *= e.stride_of(op.convs[k].label);
         std::vector<PairOp> out;
+        bool holes = false;   // positions no tap reaches: the whole output zeroed first
         for (int64_t ph = 0; ph < nph; ph++) {
             PairOp q = op;
             TensorRef& F = filt_is_r ? q.R : q.L;
@@ -401,30 +402,44 @@ struct Builder {
                 q.C.strides[pc] *= s;
                 m.O = Q;
                 if (J == 0) {
-                    // no tap reaches these positions: every term is skipped
                     empty = true;
-                    F.dims[pf] = 1;
-                    m.J = 1;
-                } else {
-                    F.buf.shift += (int64_t)(j0 * F.strides[pf] * (int64_t)esF);
-                    F.dims[pf] = J;
-                    F.strides[pf] *= s;
-                    m.J = J;
+                    continue;
                 }
+                F.buf.shift += (int64_t)(j0 * F.strides[pf] * (int64_t)esF);
+                F.dims[pf] = J;
+                F.strides[pf] *= s;
+                m.J = J;
                 const int64_t g = (r + c - j0) / s;
                 if (filt_is_r) {
                     m.gL = g;
-                    m.limR = empty ? 0 : m.J;
+                    m.limR = m.J;
                 } else {
                     m.gR = g;
-                    m.limL = empty ? 0 : m.J;
+                    m.limL = m.J;
                 }
             }
             if (none) continue;
+            if (empty) {
+                holes = true;
+                continue;
+            }
             q.macs = op.macs / nph;
             q.what = op.what + " phase " + std::to_string(ph);
-            q.generic_only = empty;
             out.push_back(q);
+        }
+        if (holes) {
+            PairOp z = op;
+            TensorRef& F = filt_is_r ? z.R : z.L;
+            for (int k : idx) {   // one tap, out of the filter's range: every term is skipped
+                ConvMap& m = z.convs[k];
+                F.dims[F.pos(m.label)] = 1;
+                m.J = 1;
+                (filt_is_r ? m.limR : m.limL) = 0;
+            }
+            z.macs = 0;
+            z.what = op.what + " zeros";
+            z.generic_only = true;
+            out.insert(out.begin(), z);
         }
         return out;
     }

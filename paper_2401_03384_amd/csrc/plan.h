@@ -55,7 +55,7 @@ struct PairOp {
     uint32_t need = 0;     // backward: run only if a wanted gradient lies below
     uint64_t macs = 0;     // multiplications of the pairwise step it belongs to
     std::string what;
-    bool generic_only = false;   // lower on the generic kernel (an op whose terms are all skipped)
+    bool generic_only = false;   // an op whose terms are all skipped: zeros (a fill, or the generic kernel)
 };
 
 struct Launch {

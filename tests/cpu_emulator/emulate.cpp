@@ -1442,6 +1442,16 @@ bool run_cred(const Launch& ln, Ctx& c) {
     return true;
 }
 
+bool run_fill(const Launch& ln, Ctx& c) {
+    const int64_t n = desc_of<int64_t>(ln);
+    bool o1;
+    Buf C = resolve(ln.c, c, 0, o1);
+    REQ(o1 && n >= 1 && (size_t)n <= C.bytes && (int64_t)ln.grid[0] * 4096 >= n && ((int64_t)ln.grid[0] - 1) * 4096 < n &&
+        ln.block[0] == 256, "fill");
+    std::memset(C.base, 0, (size_t)n);
+    return true;
+}
+
 // ---- dense-kernel launches (desc_dense.h) ------------------------------------
 // Tile geometry of the dense kernels: every staged slot a tap reads lies in
 // the tile, and the pixel tiles cover every output position once.
@@ -2001,6 +2011,7 @@ int emul_run(const char* spec, int n, const int* ranks, const int64_t* const* di
                     : v == K_CCONV ? run_cconv(ln, c)
                     : v == K_WGCONV ? run_wgconv(ln, c)
                     : v == K_GPAIR ? run_gpair(ln, c)
+                    : v == K_FILL ? run_fill(ln, c)
                     : v == K_DCONV ? run_dconv(ln, c)
                     : v == K_DWGRAD ? run_dwgrad(ln, c)
                     : v == K_RCP_MERGE ? run_rcp_merge(ln, c)
