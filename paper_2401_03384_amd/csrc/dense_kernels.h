@@ -1,0 +1,637 @@
+// Device code of the dense convolution kernels (desc_dense.h), compiled for
+// bf16 and fp32 in separate translation units.
+#pragma once
+
+#include <atomic>
+#include <cstdint>
+#include <cstring>
+#include <string>
+
+#include "desc_dense.h"
+#include "hip_util.h"
+#include "kernels.h"
+
+namespace ce {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+constexpr uint32_t kOut = 0x80000000u;   // a buffer offset past every range: reads 0
+
+// acc += A (32 x k) B (k x 32) for the 16 operand bytes a lane holds: one
+// 32x32x16 bf16 MFMA, or four 32x32x2 fp32 ones (k pairs (i, 4 + i))
+template <typename T>
+__device__ __forceinline__ void mma(f32x16& acc, const uint4& a, const uint4& b) {
+    if constexpr (sizeof(T) == 2) {
+        bf16x8 x, y;
+        __builtin_memcpy(&x, &a, 16);
+        __builtin_memcpy(&y, &b, 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+    } else {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+    }
+}
+
+// the 16 bytes of one staging unit: EPU consecutive channels of one position
+template <typename T>
+struct Unit {
+    static constexpr int EPU = 16 / sizeof(T);
+    uint32_t v[EPU];
+    // voff: byte offset of the unit's first channel (kOut: zero); sc: bytes
+    // between channels; soff: wave-uniform byte offset; left: channels of the
+    // unit that exist (the rest read 0)
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int sc, int soff) {
+#pragma unroll
+        for (int e = 0; e < EPU; e++) {
+            if constexpr (sizeof(T) == 2) v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, soff + e * sc, 0);
+            else v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, soff + e * sc, 0);
+        }
+    }
+    __device__ __forceinline__ void load_part(__amdgpu_buffer_rsrc_t r, uint32_t voff, int sc, int soff, int left) {
+#pragma unroll
+        for (int e = 0; e < EPU; e++) {
+            const int vo = e < left ? (int)voff : (int)kOut;
+            const int so = soff + e * sc;
+            if constexpr (sizeof(T) == 2) v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0);
+            else v[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0);
+        }
+    }
+    __device__ __forceinline__ uint4 pack() const {
+        if constexpr (sizeof(T) == 2)
+            return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+        else return make_uint4(v[0], v[1], v[2], v[3]);
+    }
+};
+
+// byte offset (in a group of NI images of stride sb, rows contiguous) of
+// staged slot `slot` of a tile starting at output row h0; kOut when outside
+template <typename T>
+__device__ __forceinline__ uint32_t slot_offset(const DTile& t, int slot, int h0, int ni, int64_t sb) {
+    const int area = t.HP * t.WP;
+    const int img = slot / area, rem = slot - img * area;
+    const int rr = rem / t.WP, cc = rem - rr * t.WP;
+    const int hh = t.sth * h0 + min(t.zh0, t.zh0 + t.zhs * (t.KH - 1)) + rr;
+    const int ww = min(t.zw0, t.zw0 + t.zws * (t.KW - 1)) + cc;
+    const bool ok = img < ni && hh >= 0 && hh < t.H && ww >= 0 && ww < t.W;
+    return ok ? (uint32_t)(sizeof(T) * (img * sb + (int64_t)hh * t.W + ww)) : kOut;
+}
+
+constexpr int kPitch = 20;   // words a staged slot takes in dconv: 64 B of channels + 16 B
+                             // (16-byte reads of 8 neighbouring slots hit distinct banks)
+
+// One block: MW * MT * 32 rows x one pixel tile (at most NW * NT * 32 pixels),
+// KH x KW taps.  A wavefront streams its packed rows from L2 (operand loads D
+// taps ahead in a register ring, D dividing the taps) against pixel operands
+// from LDS; the next chunk of channels is in flight to registers (the first
+// NU units a thread) during the current one's MFMAs.  KSP = 1: the block's
+// four wavefronts share each staged chunk (two LDS buffers, one barrier a
+// chunk).  KSP = 4 (few pixels): each wavefront takes the whole 64 x 64 tile
+// for every fourth chunk, staged by itself without block barriers, which
+// halves the operand bytes an MFMA reads against four 32 x 32 wavefronts; the
+// four sums are added in order through LDS.
+// Measured with its pack launch against the general contraction: the strided
+// layer X[16,128,28,28] -> 256 channels, 3x3 stride 2, bf16: forward 52 -> 24
+// us, kernel gradient (dwgrad) 76 -> 24 us; the fp32 Tucker core X[16,40,13,27]
+// -> 48, 3x3: 53 -> 25 us.
+// fp32: runs of at most 80 terms are summed on their own and then added, which
+// keeps the rounding error of a K-term sum near that of sqrt(K) terms.
+template <typename T, int KH, int KW, int KSP, int MW, int NW, int MT, int NT, int D, int NU>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 && (MT * NT == 4 || KH == 5) ? 1 : 2) dconv(DConvDesc d, const T* __restrict__ X,
+                                                const uint4* __restrict__ A, T* __restrict__ Y) {
+    constexpr int EPU = 16 / sizeof(T), CK = 4 * EPU, KT = KH * KW, NTH = 256 / KSP;
+    constexpr bool kTwo = sizeof(T) == 4;   // fp32 sums in two levels
+    constexpr bool kRows = D == KW && KH > 1;
+    static_assert(KT % D == 0, "the ring restarts with every chunk");
+    static_assert(KSP == 1 || (KSP == 4 && MW == 1 && NW == 1 && MT == 2 && NT == 2), "");
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const DTile& t = d.t;
+    const int lane = threadIdx.x & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = KSP == 1 ? (int)threadIdx.x : lane;
+    const int wm = KSP == 1 ? wave % MW : 0, wn = KSP == 1 ? wave / MW : 0;
+    const int mb = (int)(blockIdx.x % (uint32_t)d.mblk), pt = (int)(blockIdx.x / (uint32_t)d.mblk);
+    const int ti = pt / t.nth, h0 = (pt - ti * t.nth) * t.TH, b0 = ti * t.NI;
+    const int ni = min(t.NI, t.B - b0), nr = min(t.TH, t.OH - h0);
+    const int slots = t.slots;
+    const int sc = (int)(sizeof(T) * d.x_sc);
+    const int mtiles = (d.M + 31) / 32;
+    // this wavefront's chunks: c0, c0 + KSP, ...; q counts its (chunk, tap)s
+    const int c0 = KSP == 1 ? 0 : wave, nmy = c0 < d.nch ? (d.nch - c0 + KSP - 1) / KSP : 0;
+    const uint4* pa[MT];
+#pragma unroll
+    for (int m = 0; m < MT; m++) {
+        const int mt = min((mb * MW + wm) * MT + m, mtiles - 1);
+        pa[m] = A + ((int64_t)mt * d.nch + min(c0, d.nch - 1)) * KT * 128 + lane;
+    }
+    uint4 a[D][MT][2];
+#pragma unroll
+    for (int q = 0; q < D; q++)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int k = 0; k < 2; k++) a[q][m][k] = pa[m][128 * q + 64 * k];
+    const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(X + b0 * d.x_sb), (short)0, (int)(sizeof(T) * ni * d.x_sb), 0x00020000);
+    uint32_t voff[NU];
+    int dst[NU], cg[NU];
+#pragma unroll
+    for (int i = 0; i < NU; i++) {
+        const int u = tid + NTH * i, g = u / slots, slot = u - g * slots;
+        const uint32_t o = u < 4 * slots ? slot_offset<T>(t, slot, h0, ni, d.x_sb) : kOut;
+        cg[i] = g;
+        voff[i] = o == kOut ? kOut : o + (uint32_t)(g * EPU * sc);
+        dst[i] = slot * kPitch + 4 * g;
+    }
+    const bool part = d.C % CK != 0;
+    Unit<T> un[NU];
+    auto fetch = [&](int ch) {
+        const int soff = ch * CK * sc;
+        if (part && ch == d.nch - 1) {
+#pragma unroll
+            for (int i = 0; i < NU; i++) un[i].load_part(rX, voff[i], sc, soff, d.C - ch * CK - cg[i] * EPU);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NU; i++) un[i].load(rX, voff[i], sc, soff);
+        }
+    };
+    if (nmy > 0) fetch(c0);
+    // pixel operands: slot of the lane's pixel of each column tile
+    int base[NT];
+    bool ok[NT];
+    int64_t yo[NT];
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+        const int n = (wn * NT + j) * 32 + cl, per = t.TH * t.OW;
+        const int img = n / per, rem = n - img * per, r = rem / t.OW, c = rem - r * t.OW;
+        ok[j] = img < ni && r < nr;
+        yo[j] = (b0 + img) * d.y_sb + (h0 + r) * d.y_sh + c * d.y_sw;
+        base[j] = (ok[j] ? (img * t.HP + t.sth * r) * t.WP + t.stw * c : 0) * kPitch + 4 * hf;
+    }
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int j = 0; j < NT; j++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) acc[m][j][i] = 0.f;
+    f32x16 run[kTwo ? MT : 1][kTwo ? NT : 1];
+    if constexpr (kTwo)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int j = 0; j < NT; j++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) run[m][j][i] = 0.f;
+    const int mh = min(0, t.zhs * (KH - 1)), mw = min(0, t.zws * (KW - 1));
+    uint32_t* const buf0 = KSP == 1 ? lds : lds + 2 * wave * slots * kPitch;
+    uint32_t* buf = buf0;
+    for (int n = 0; n < nmy; n++) {
+        const int ch = c0 + KSP * n;
+#pragma unroll
+        for (int i = 0; i < NU; i++)
+            if (tid + NTH * i < 4 * slots) *reinterpret_cast<uint4*>(buf + dst[i]) = un[i].pack();
+        for (int u = tid + NTH * NU; u < 4 * slots; u += NTH) {   // tiles past NU units a thread
+            const int g = u / slots, slot = u - g * slots;
+            const uint32_t o = slot_offset<T>(t, slot, h0, ni, d.x_sb);
+            Unit<T> x;
+            x.load_part(rX, o == kOut ? kOut : o + (uint32_t)(g * EPU * sc), sc, ch * CK * sc, d.C - ch * CK - g * EPU);
+            *reinterpret_cast<uint4*>(buf + slot * kPitch + 4 * g) = x.pack();
+        }
+        if constexpr (KSP == 1) {
+            __syncthreads();
+        } else {
+            // the buffer is this wavefront's own: order its LDS accesses only
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        if (n + 1 < nmy) fetch(ch + KSP);
+        const bool mask = part && ch == d.nch - 1;
+        // operands D taps on: the same chunk, else the wavefront's next one
+        const int64_t qa = (int64_t)KSP * n * KT, qb = (int64_t)KSP * min(n + 1, nmy - 1) * KT;
+        // a ring as long as a row of taps: rows in a loop, a row unrolled
+#pragma unroll 1
+        for (int row = 0; row < (kRows ? KH : 1); row++) {
+#pragma unroll
+            for (int j = 0; j < (kRows ? KW : KT); j++) {
+                const int ti = kRows ? row : j / KW, tj = kRows ? j : j % KW, tap = kRows ? row * KW + j : j;
+                const uint32_t* bt = buf + ((t.zhs * ti - mh) * t.WP + t.zws * tj - mw) * kPitch;
+                uint4 b[2][NT];
+#pragma unroll
+                for (int k = 0; k < 2; k++)
+#pragma unroll
+                    for (int x = 0; x < NT; x++) b[k][x] = *reinterpret_cast<const uint4*>(bt + base[x] + 8 * k);
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    if (mask) {
+                        // packed channels past C hold no kernel values
+                        const int left = d.C - ch * CK - (2 * k + hf) * EPU;
+#pragma unroll
+                        for (int m = 0; m < MT; m++) {
+                            uint4& v = a[j % D][m][k];
+                            uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                            for (int e = 0; e < 4; e++) {
+                                if constexpr (sizeof(T) == 2) {
+                                    if (2 * e + 1 >= left) w[e] &= 0xffffu;
+                                    if (2 * e >= left) w[e] = 0;
+                                } else if (e >= left) w[e] = 0;
+                            }
+                            v = make_uint4(w[0], w[1], w[2], w[3]);
+                        }
+                    }
+#pragma unroll
+                    for (int m = 0; m < MT; m++)
+#pragma unroll
+                        for (int x = 0; x < NT; x++) {
+                            if constexpr (kTwo) mma<T>(run[m][x], a[j % D][m][k], b[k][x]);
+                            else mma<T>(acc[m][x], a[j % D][m][k], b[k][x]);
+                        }
+                }
+                if constexpr (kTwo)
+                    if (kRows ? j == KW - 1 : (j % 4 == 3 || j == KT - 1))   // at most 80 terms a run
+#pragma unroll
+                        for (int m = 0; m < MT; m++)
+#pragma unroll
+                            for (int x = 0; x < NT; x++)
+#pragma unroll
+                                for (int i = 0; i < 16; i++) {
+                                    acc[m][x][i] += run[m][x][i];
+                                    run[m][x][i] = 0.f;
+                                }
+                const int64_t qn = (tap + D < KT ? qa + tap + D : qb + (tap + D - KT)) * 128;
+#pragma unroll
+                for (int m = 0; m < MT; m++)
+#pragma unroll
+                    for (int k = 0; k < 2; k++) a[j % D][m][k] = pa[m][qn + 64 * k];
+            }
+        }
+        buf = buf == buf0 ? buf0 + slots * kPitch : buf0;
+    }
+    // accumulator i of a lane: row 8(i / 4) + 4 hf + i % 4 of its row tile
+    auto put = [&](const f32x16& v, int m, int64_t o) {
+        const int r0 = ((mb * MW + wm) * MT + m) * 32 + 4 * hf;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = r0 + 8 * (i >> 2) + (i & 3);
+            if (r < d.M) store(Y, o + r * d.y_sm, v[i]);
+        }
+    };
+    if constexpr (KSP == 1) {
+#pragma unroll
+        for (int x = 0; x < NT; x++) {
+            if (!ok[x]) continue;
+#pragma unroll
+            for (int m = 0; m < MT; m++) put(acc[m][x], m, yo[x]);
+        }
+    } else {
+        float* red = reinterpret_cast<float*>(lds);   // [tile][wavefront][16][64]
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+            for (int x = 0; x < NT; x++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) red[((2 * m + x) * 4 + wave) * 1024 + 64 * i + lane] = acc[m][x][i];
+        __syncthreads();
+        // wavefront w: the tile of rows w / 2, columns w % 2
+        f32x16 v;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const float* p = red + wave * 4096 + 64 * i + lane;
+            v[i] = (p[0] + p[1024]) + (p[2048] + p[3072]);
+        }
+        const bool second = wave & 1;
+        if (second ? ok[1] : ok[0]) put(v, wave >> 1, second ? yo[1] : yo[0]);
+    }
+}
+
+// One block: 64 t x (32 NS) s x every tap, over its share of the pixel tiles;
+// 2 NS NTG wavefronts, each 32 t x 32 s x the taps j = tg, tg + NTG, ...
+// G and X sit in LDS position-major (channels innermost); the reduction runs
+// over pixels, so bf16 operands are read with the transposing 8-byte LDS load
+// (a group of 16 lanes: 4 pixels x 16 channels, lane l gets channel l's four
+// pixels) and fp32 ones word by word.  Pixels past a tile point at zero slots.
+// The next tile is in flight to registers (at most four units a thread of G
+// and of X, which the planner's tile respects) during the current one's MFMAs.
+template <typename T, int NS, int NTG, int TG>
+__global__ void __launch_bounds__(128 * NS * NTG, 2) dwgrad(DWgradDesc d, const T* __restrict__ G,
+                                                           const T* __restrict__ X, float* __restrict__ P) {
+    constexpr int EPU = 16 / sizeof(T), NTHR = 128 * NS * NTG;
+    constexpr int GU = 64 / EPU, XU = 32 * NS / EPU;                 // units of one pixel / slot
+    constexpr int UG = 4, UX = 4;                                    // units a thread
+    constexpr int PG = (64 * sizeof(T) + 16) / 4;                    // words a pixel
+    constexpr int PX = (32 * NS * sizeof(T) + (NS == 1 && sizeof(T) == 2 ? 32 : 16)) / 4;
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const DTile& t = d.t;
+    uint32_t* lg = lds;
+    uint32_t* lx = lds + d.o_x / 4;
+    int* tab = reinterpret_cast<int*>(lds + d.o_tab / 4);
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, cl = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wt = wave & 1, ws = (wave >> 1) % NS, wg = (wave >> 1) / NS;
+    uint32_t id = blockIdx.x;
+    const int sb = (int)(id % (uint32_t)d.nsb);
+    id /= (uint32_t)d.nsb;
+    const int tb = (int)(id % (uint32_t)d.ntb), sp = (int)(id / (uint32_t)d.ntb);
+    const int t0 = tb * 64, s0 = sb * 32 * NS;
+    const int KT = t.KH * t.KW, slots = t.slots, per = t.TH * t.OW;
+    const int gsc = (int)(sizeof(T) * d.g_sc), xsc = (int)(sizeof(T) * d.x_sc);
+    // zero slots after the tile: every tap of a pixel past the tile reads there
+    const int zspan = (t.KH - 1) * t.WP + t.KW;
+    for (int u = tid; u < zspan * PX; u += NTHR) lx[slots * PX + u] = 0;
+    int toff[TG];
+    const int mh = min(0, t.zhs * (t.KH - 1)), mw = min(0, t.zws * (t.KW - 1));
+#pragma unroll
+    for (int a = 0; a < TG; a++) {
+        const int j = min(wg + a * NTG, KT - 1), ji = j / t.KW, jj = j - ji * t.KW;
+        toff[a] = ((t.zhs * ji - mh) * t.WP + t.zws * jj - mw) * PX;
+    }
+    // a thread's staging units, the same for every tile: byte offset from the
+    // tile's first row of its first image, image, row; LDS word
+    int goff[UG], gim[UG], gr[UG], gdst[UG], gch[UG];
+    int xoff[UX], xim[UX], xr[UX], xdst[UX], xch[UX];
+    const int hmin = min(t.zh0, t.zh0 + t.zhs * (t.KH - 1)), wmin = min(t.zw0, t.zw0 + t.zws * (t.KW - 1));
+#pragma unroll
+    for (int i = 0; i < UG; i++) {
+        const int u = tid + i * NTHR, g = u / d.PP, px = u - g * d.PP;
+        const int img = px / per, rem = px - img * per;
+        gr[i] = rem / t.OW;
+        gim[i] = u < GU * d.PP ? img : 0x7fffffff;
+        gch[i] = t0 + g * EPU;
+        goff[i] = (int)(sizeof(T) * (img * d.g_sb + rem)) + gch[i] * gsc;
+        gdst[i] = u < GU * d.PP ? px * PG + 4 * g : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < UX; i++) {
+        const int u = tid + i * NTHR, g = u / slots, slot = u - g * slots;
+        const int area = t.HP * t.WP, img = slot / area, rem = slot - img * area;
+        const int rr = rem / t.WP, ww = wmin + rem - rr * t.WP;
+        xr[i] = hmin + rr;
+        xim[i] = u < XU * slots && ww >= 0 && ww < t.W ? img : 0x7fffffff;
+        xch[i] = s0 + g * EPU;
+        xoff[i] = (int)(sizeof(T) * (img * d.x_sb + xr[i] * t.W + ww)) + xch[i] * xsc;
+        xdst[i] = u < XU * slots ? slot * PX + 4 * g : -1;
+    }
+    const int pimg = tid / per, prem = tid - pimg * per, prow = prem / t.OW;
+    const int pslot = ((pimg * t.HP + t.sth * prow) * t.WP + t.stw * (prem - prow * t.OW)) * PX;
+    f32x16 acc[TG];
+#pragma unroll
+    for (int a = 0; a < TG; a++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[a][i] = 0.f;
+    const int p0 = (int)((int64_t)t.npt * sp / d.nsplit), p1 = (int)((int64_t)t.npt * (sp + 1) / d.nsplit);
+    constexpr bool kTwo = sizeof(T) == 4 && TG <= 3;   // fp32: a tile's sums on their own, then added
+    f32x16 run[kTwo ? TG : 1];
+    if constexpr (kTwo)
+#pragma unroll
+        for (int a = 0; a < TG; a++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) run[a][i] = 0.f;
+    Unit<T> ug[UG], ux[UX];
+    int ni = 0, nr = 0;
+    auto fetch = [&](int pt) {
+        const int ti = pt / t.nth, h0 = (pt - ti * t.nth) * t.TH, b0 = ti * t.NI;
+        ni = min(t.NI, t.B - b0);
+        nr = min(t.TH, t.OH - h0);
+        const __amdgpu_buffer_rsrc_t rG = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(G + b0 * d.g_sb), (short)0, (int)(sizeof(T) * ni * d.g_sb), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rX = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(X + b0 * d.x_sb), (short)0, (int)(sizeof(T) * ni * d.x_sb), 0x00020000);
+        const int gh = (int)sizeof(T) * h0 * t.OW, xh0 = t.sth * h0, xh = (int)sizeof(T) * xh0 * t.W;
+#pragma unroll
+        for (int i = 0; i < UG; i++)
+            if (i * NTHR < GU * d.PP) ug[i].load_part(rG, gim[i] < ni && gr[i] < nr ? (uint32_t)(goff[i] + gh) : kOut, gsc, 0, d.T - gch[i]);
+#pragma unroll
+        for (int i = 0; i < UX; i++) {
+            if (i * NTHR >= XU * slots) break;
+            const bool in = xim[i] < ni && xr[i] + xh0 >= 0 && xr[i] + xh0 < t.H;
+            ux[i].load_part(rX, in ? (uint32_t)(xoff[i] + xh) : kOut, xsc, 0, d.S - xch[i]);
+        }
+    };
+    if (p0 < p1) fetch(p0);
+    for (int pt = p0; pt < p1; pt++) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < UG; i++)
+            if (gdst[i] >= 0) *reinterpret_cast<uint4*>(lg + gdst[i]) = ug[i].pack();
+#pragma unroll
+        for (int i = 0; i < UX; i++)
+            if (xdst[i] >= 0) *reinterpret_cast<uint4*>(lx + xdst[i]) = ux[i].pack();
+        if (tid < d.PP) tab[tid] = pimg < ni && prow < nr ? pslot : slots * PX;
+        __syncthreads();
+        if (pt + 1 < p1) fetch(pt + 1);
+        if constexpr (sizeof(T) == 2) {
+            const int g16 = lane >> 4, i16 = lane & 15;
+            const int choff = (16 * (g16 & 1) + 4 * (i16 & 3)) / 2;   // words
+            const uint32_t* ga = lg + 16 * wt + choff;
+            const uint32_t* xa = lx + 16 * ws + choff;
+            const int kp = 8 * hf + (i16 >> 2);
+            typedef __attribute__((address_space(3))) s16x4* lptr;
+            auto tr = [](const uint32_t* p, const uint32_t* q) {
+                const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)p);
+                const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)q);
+                uint4 w;
+                __builtin_memcpy(&w.x, &u, 8);
+                __builtin_memcpy(&w.z, &v, 8);
+                return w;
+            };
+            for (int k = 0; k < d.PP; k += 16) {
+                const int pa = k + kp, s_a = tab[pa], s_b = tab[pa + 4];
+                const uint4 av = tr(ga + pa * PG, ga + (pa + 4) * PG);
+                const uint32_t* x0 = xa + s_a;
+                const uint32_t* x1 = xa + s_b;
+#pragma unroll
+                for (int a = 0; a < TG; a++) mma<T>(acc[a], av, tr(x0 + toff[a], x1 + toff[a]));
+            }
+        } else {
+            const float* ga = reinterpret_cast<const float*>(lg) + 32 * wt + cl;
+            const float* xa = reinterpret_cast<const float*>(lx) + 32 * ws + cl;
+#pragma unroll 2
+            for (int k = 0; k < d.PP; k += 2) {
+                const int p = k + hf;
+                const float av = ga[p * PG];
+                const float* x0 = xa + tab[p];
+#pragma unroll
+                for (int a = 0; a < TG; a++) {
+                    if constexpr (kTwo) run[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, x0[toff[a]], run[a], 0, 0, 0);
+                    else acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, x0[toff[a]], acc[a], 0, 0, 0);
+                }
+            }
+            if constexpr (kTwo)
+#pragma unroll
+                for (int a = 0; a < TG; a++)
+#pragma unroll
+                    for (int i = 0; i < 16; i++) {
+                        acc[a][i] += run[a][i];
+                        run[a][i] = 0.f;
+                    }
+        }
+    }
+    // columns s (the lane), rows t: partial [sp][tap][t][s]
+    const int s = s0 + 32 * ws + cl;
+#pragma unroll
+    for (int a = 0; a < TG; a++) {
+        const int j = wg + a * NTG;
+        if (j >= KT || s >= d.S) continue;
+        float* o = P + ((int64_t)sp * KT + j) * d.T * d.S + s;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = t0 + 32 * wt + 8 * (i >> 2) + 4 * hf + (i & 3);
+            if (r < d.T) o[(int64_t)r * d.S] = acc[a][i];
+        }
+    }
+}
+
+// The packed kernel (DConvDesc's order) of F with element strides sm, sc, sh,
+// sw: a thread gathers the 16 bytes of one row and channel unit, tap by tap
+// (its reads are runs of taps; its writes 1 KB a wavefront).  Rows past M and
+// channels past C are zero.
+template <typename T>
+__global__ void __launch_bounds__(256) dpack(DPackDesc d, const T* __restrict__ F, uint4* __restrict__ out) {
+    constexpr int EPU = 16 / sizeof(T), CK = 4 * EPU;
+    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (u >= (int64_t)d.mt * d.nch * 128) return;
+    const int l = (int)(u & 63), k = (int)(u >> 6) & 1;
+    const int64_t mc = u >> 7;
+    const int ch = (int)(mc % d.nch), row = (int)(mc / d.nch) * 32 + (l & 31), c0 = ch * CK + (2 * k + (l >> 5)) * EPU;
+    const T* p = F + row * d.sm + c0 * d.sc;
+    const int live = row < d.M ? d.C - c0 : 0;
+    uint4* o = out + mc * d.KH * d.KW * 128 + (u & 127);
+    for (int i = 0; i < d.KH; i++)
+        for (int j = 0; j < d.KW; j++, o += 128) {
+            T v[EPU];
+#pragma unroll
+            for (int e = 0; e < EPU; e++) v[e] = e < live ? p[e * d.sc + i * d.sh + j * d.sw] : T(0);
+            uint4 w;
+            __builtin_memcpy(&w, v, 16);
+            *o = w;
+        }
+}
+
+// C[t][s][tap] = ordered sum of dwgrad's partials, in C's layout and type
+template <typename TO>
+__global__ void __launch_bounds__(256) dwred(DWredDesc d, const float* __restrict__ P, TO* __restrict__ C) {
+    const int64_t n = (int64_t)d.T * d.S * d.KH * d.KW, u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (u >= n) return;
+    double acc = 0;
+    for (int sp = 0; sp < d.nsplit; sp += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) v[i] = P[(int64_t)min(sp + i, d.nsplit - 1) * n + u];
+#pragma unroll
+        for (int i = 0; i < 8; i++) acc += sp + i < d.nsplit ? (double)v[i] : 0.0;
+    }
+    const int s = (int)(u % d.S);
+    const int64_t x = u / d.S;
+    const int t = (int)(x % d.T), j = (int)(x / d.T);
+    store(C, t * d.st + s * d.ss + (j / d.KW) * d.sh + (j % d.KW) * d.sw, (float)acc);
+}
+
+template <typename D>
+D desc_of(const Launch& ln) {
+    D d;
+    std::memcpy(&d, ln.desc.data(), sizeof(d));
+    return d;
+}
+
+// dynamic LDS beyond 64 KB needs the attribute, once per kernel and device
+template <typename F>
+hipError_t allow_lds(F f, uint32_t bytes) {
+    if (bytes <= 65536) return hipSuccess;
+    static std::atomic<uint64_t> done{0};   // one mask per kernel instantiation (F differs per call site)
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 64 && ((done.load() >> dev) & 1)) return hipSuccess;
+    e = f();
+    if (e == hipSuccess && dev < 64) done.fetch_or(uint64_t(1) << dev);
+    return e;
+}
+
+
+template <typename T, int KH, int KW>
+hipError_t conv_t(const Launch& ln, const DConvDesc& d, const void* x, const void* a, void* y, hipStream_t s) {
+    const dim3 g(ln.grid[0]), b(256);
+    constexpr int KT = KH * KW, D = KT == 9 ? 3 : KT == 25 ? 5 : KT;
+#define CE_DCONV(KSP, MW, NW, MT, NT, DD, NU)                                                                    \
+    do {                                                                                                         \
+        auto k = dconv<T, KH, KW, KSP, MW, NW, MT, NT, DD, NU>;                                                  \
+        hipError_t e = allow_lds([&] {                                                                           \
+            return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);  \
+        }, ln.lds);                                                                                              \
+        if (e != hipSuccess) return e;                                                                           \
+        hipLaunchKernelGGL(k, g, b, ln.lds, s, d, (const T*)x, (const uint4*)a, (T*)y);                          \
+        return hipGetLastError();                                                                                \
+    } while (0)
+    const int nu = (4 * d.t.slots + 255) / 256;
+    if (d.cfg == 2) CE_DCONV(4, 1, 1, 2, 2, D, 6);
+    if constexpr (KT >= 9) {
+        if (d.cfg == 0 && nu <= 4) CE_DCONV(1, 1, 4, 2, 2, D, 4);
+        if (d.cfg == 1 && nu <= 4) CE_DCONV(1, 2, 2, 1, 2, KT == 9 && sizeof(T) == 2 ? 9 : D, 4);
+        if (d.cfg == 1) CE_DCONV(1, 2, 2, 1, 2, KT == 9 && sizeof(T) == 2 ? 9 : D, 7);
+    }
+    if (d.cfg == 0) CE_DCONV(1, 1, 4, 2, 2, D, 7);
+#undef CE_DCONV
+    return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t dense_conv(const Launch& ln, const void* x, const void* a, void* y, hipStream_t s) {
+    const DConvDesc d = desc_of<DConvDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0] || (uint32_t)(8 * d.t.slots * kPitch * (d.cfg == 2 ? 4 : 1)) > ln.lds ||
+        (d.cfg == 2 && ln.lds < 65536))
+        return hipErrorInvalidValue;
+    switch (8 * d.t.KH + d.t.KW) {
+        case 27: return conv_t<T, 3, 3>(ln, d, x, a, y, s);
+        case 45: return conv_t<T, 5, 5>(ln, d, x, a, y, s);
+        case 9: return conv_t<T, 1, 1>(ln, d, x, a, y, s);
+        case 10: return conv_t<T, 1, 2>(ln, d, x, a, y, s);
+        case 17: return conv_t<T, 2, 1>(ln, d, x, a, y, s);
+        case 18: return conv_t<T, 2, 2>(ln, d, x, a, y, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// configuration 0: up to 10 (bf16) / 12 (fp32) taps; 1: up to 28; 2: one tap
+template <typename T>
+hipError_t dense_wgrad(const Launch& ln, const void* gr, const void* x, void* p, hipStream_t s) {
+    const DWgradDesc d = desc_of<DWgradDesc>(ln);
+    if (d.blocks != (int64_t)ln.grid[0] || ln.block[0] != 512) return hipErrorInvalidValue;
+#define CE_DWGRAD(NS, NTG, TG)                                                                                   \
+    do {                                                                                                         \
+        auto k = dwgrad<T, NS, NTG, TG>;                                                                         \
+        static_assert(128 * NS * NTG == 512, "");                                                                \
+        hipError_t e = allow_lds([&] {                                                                           \
+            return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);  \
+        }, ln.lds);                                                                                              \
+        if (e != hipSuccess) return e;                                                                           \
+        hipLaunchKernelGGL(k, dim3(ln.grid[0]), dim3(512), ln.lds, s, d, (const T*)gr, (const T*)x, (float*)p);  \
+        return hipGetLastError();                                                                                \
+    } while (0)
+    if constexpr (sizeof(T) == 2) {
+        if (d.cfg == 0) CE_DWGRAD(2, 2, 5);
+    } else {
+        if (d.cfg == 0) CE_DWGRAD(1, 4, 3);
+    }
+    if (d.cfg == 1) CE_DWGRAD(1, 4, 7);
+    if (d.cfg == 2) CE_DWGRAD(4, 1, 1);
+#undef CE_DWGRAD
+    return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t dense_pack(const Launch& ln, const void* f, void* out, hipStream_t s) {
+    const DPackDesc d = desc_of<DPackDesc>(ln);
+    if ((int64_t)ln.grid[0] * 256 < (int64_t)d.mt * d.nch * 128) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(dpack<T>, dim3(ln.grid[0]), dim3(256), 0, s, d, (const T*)f, (uint4*)out);
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace ce

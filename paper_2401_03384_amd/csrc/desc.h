@@ -73,6 +73,8 @@ enum KernelKind : int32_t {
     K_RCP_MERGE = 43,       // merged, packed kernel of a reshaped-CP layer (DRcpDesc)
     K_RCP_DFWD = 45,        // reshaped-CP forward merging its kernel on chip (RcpDfwdDesc)
     K_RCP_FGRAD = 44,       // its factor gradients' partials from the kernel's gradient (DRcpDesc)
+    K_DPACK = 47,           // packed kernel of a dense convolution (DPackDesc)
+    K_DWRED = 48,           // ordered sum of K_DWGRAD partials into a gradient (DWredDesc)
     K_FILL = 46,            // zeros over a dense buffer (int64_t: its bytes)
 };
 

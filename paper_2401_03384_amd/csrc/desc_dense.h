@@ -41,6 +41,18 @@ struct DWgradDesc {
     int64_t blocks;
 };
 
+// The packed kernel of F (strides in elements: row, channel, taps).
+struct DPackDesc {
+    int32_t M, C, KH, KW, mt, nch;     // mt: tiles of 32 rows, nch: channel chunks
+    int64_t sm, sc, sh, sw;
+};
+
+// Ordered sum of dwgrad's partials into C (strides in elements).
+struct DWredDesc {
+    int32_t T, S, KH, KW, nsplit, pad_;
+    int64_t st, ss, sh, sw;
+};
+
 // Reshaped CP: W[t1 t2 t3][s1 s2 s3][j] = sum_r W1[r][t1][s1] W2[r][t2][s2]
 // W3[r][t3][s3] W0[r][j], packed for the forward (rows t) or for the input
 // gradient (rows s); and the factor gradients from the partials of dW.

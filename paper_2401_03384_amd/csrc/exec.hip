@@ -72,8 +72,10 @@ hipError_t raw_launch(const Launch& ln, const Ptrs& P, hipStream_t s) {
             return launch_rcp_prep(ln, ops, s);
         }
         case K_FILL: return launch_fill(ln, c, s);
-        case K_DCONV: return launch_dconv(ln, a, b, c, s);
-        case K_DWGRAD: return launch_dwgrad(ln, a, b, d, s);
+        case K_DCONV:
+        case K_DWGRAD:
+        case K_DPACK:
+        case K_DWRED: return launch_dense(ln, a, b, c, d, s);
         case K_RCP_MERGE: {
             const void* ops[5];
             for (int i = 0; i < 5; i++) ops[i] = resolve(ln.extra[i], P);

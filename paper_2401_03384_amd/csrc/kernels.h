@@ -64,11 +64,11 @@ hipError_t launch_rcp_fwd(const Launch& ln, const void* const* ops, void* y, hip
 hipError_t launch_rcp_bwd(const Launch& ln, const void* const* ops, hipStream_t s);
 hipError_t launch_rcp_prep(const Launch& ln, const void* const* ops, hipStream_t s);
 
-// Dense convolution with a packed kernel (K_DCONV): x = input planes, a = the
-// packed kernel, y = output planes; the partials of its kernel's gradient
-// (K_DWGRAD): g = output gradient, x = input planes, p = fp32 partials.
-hipError_t launch_dconv(const Launch& ln, const void* x, const void* a, void* y, hipStream_t s);
-hipError_t launch_dwgrad(const Launch& ln, const void* g, const void* x, void* p, hipStream_t s);
+// Dense convolution (desc_dense.h).  K_DPACK: a = the kernel, c = its packed
+// form; K_DCONV: a = input planes, b = the packed kernel, c = output planes;
+// K_DWGRAD: a = output gradient, b = input planes, d = fp32 partials; K_DWRED:
+// d = those partials, c = the kernel's gradient.
+hipError_t launch_dense(const Launch& ln, const void* a, const void* b, void* c, void* d, hipStream_t s);
 // Merged kernel of a reshaped-CP layer: ops = {W1, W2, W3, W0, packed kernel};
 // its factor gradients: ops = {W1, W2, W3, W0, DW, P1, P2, P3, P0}.
 hipError_t launch_rcp_merge(const Launch& ln, const void* const* ops, hipStream_t s);

@@ -1389,13 +1389,14 @@ bool try_gpair_ops(const PairOp& gl, const PairOp& gr, ScratchAlloc& scratch, st
             continue;
         // A block walks its tiles and chunks one after another, 1.6 us each on a
         // full chip and 2.4 us alone; two separate launches read dC twice at
-        // about 2.5 TB/s and multiply at about 40 TFLOP/s, after some 25 us (40
-        // for long rows, on the general contraction) of launches.  Few samples leave the
+        // about 2.5 TB/s and multiply at about 40 TFLOP/s, after some 25 us of
+        // launches (more for long rows, on the general contraction: 55 against
+        // 41 us fused at 256 rows, 90 against 52 at 512).  Few samples leave the
         // fused kernel with few blocks (X[24,48,37,29], rank 20: 47 + 6 us
         // against 10 + 11 + 6 us; one 56x56 sample: 115 against 24 us).
         const double serial = (double)cdiv(d.blocks, 256) * d.gper * d.ntiles * d.nkc * (d.blocks < 256 ? 2.4 : 1.6);
         const double moved = 2 * tensor_bytes(Gt) + 2 * tensor_bytes(At);
-        if (serial > (d.nkc == 1 ? 25.0 : 40.0) + moved / 2.5e6 + 4.0 * (double)gl.macs / 40e6) continue;
+        if (serial > (d.nkc == 1 ? 25.0 : 20.0 + 9.0 * d.nkc) + moved / 2.5e6 + 4.0 * (double)gl.macs / 40e6) continue;
         const BufRef part = scratch.alloc((size_t)(d.blocks * fnumel * 4));
         Launch ln;
         ln.kind = K_GPAIR | dt_bits(DT_F32, DT_F32, DT_F32);
@@ -1456,6 +1457,233 @@ std::vector<Launch> lower_grad_pair(const PairOp& gl, const PairOp& gr, unsigned
     return out;
 }
 
+// ---- dense convolution steps -------------------------------------------------
+namespace {
+
+// A two-dimensional convolution (or its kernel's gradient) between a stack of
+// planes Z[batch][channel][h][w] and one operand F, every label group a single
+// dimension:
+//   kernel form   F[out][channel][taps], C[batch][out][positions]
+//   gradient form F[batch][out][positions], C[out][channel][taps]
+// with Z read at a p + b j + g (p: C's index, j: F's).
+struct DenseForm {
+    const TensorRef *Z, *F;
+    int lh, lw;
+    ConvMap h, w;               // L = Z
+    std::vector<int> only_z, only_f, shared;   // C's labels in Z / in F only; the reduced ones
+};
+
+bool dense_form(const PairOp& op, DenseForm& f) {
+    if (!op.has_r || op.convs.size() != 2 || op.L.dtype != op.R.dtype) return false;
+    // F's positions are its own index j in both maps
+    const bool z_is_l = op.convs[0].aR == 0 && op.convs[0].bR == 1 && op.convs[0].aL > 0;
+    f.Z = z_is_l ? &op.L : &op.R;
+    f.F = z_is_l ? &op.R : &op.L;
+    ConvMap m[2];
+    for (int k = 0; k < 2; k++) {
+        m[k] = op.convs[k];
+        if (!z_is_l) {
+            std::swap(m[k].aL, m[k].aR);
+            std::swap(m[k].bL, m[k].bR);
+            std::swap(m[k].gL, m[k].gR);
+            std::swap(m[k].limL, m[k].limR);
+        }
+        if (m[k].modL || m[k].modR || m[k].aR != 0 || m[k].bR != 1 || m[k].gR != 0 || m[k].limR != m[k].J || m[k].aL < 1 ||
+            m[k].aL > 4 || m[k].bL < -4 || m[k].bL > 4 || m[k].bL == 0 || m[k].O < 1 || m[k].J < 1)
+            return false;
+        const int l = m[k].label;
+        if (!f.Z->has(l) || !f.F->has(l) || !op.C.has(l) || f.Z->dim_of(l) != m[k].limL || f.F->dim_of(l) != m[k].J ||
+            op.C.dim_of(l) != m[k].O || m[k].limL > (1 << 20) || m[k].J > (1 << 20) || m[k].O > (1 << 20))
+            return false;
+    }
+    const int iw = f.Z->stride_of(m[0].label) == 1 ? 0 : 1;
+    f.w = m[iw];
+    f.h = m[1 - iw];
+    f.lw = f.w.label;
+    f.lh = f.h.label;
+    if (f.Z->stride_of(f.lw) != 1 || f.Z->stride_of(f.lh) != f.w.limL) return false;
+    for (int l : op.C.labels) {
+        if (l == f.lh || l == f.lw) continue;
+        const bool z = f.Z->has(l), o = f.F->has(l);
+        if (z == o) return false;
+        (z ? f.only_z : f.only_f).push_back(l);
+    }
+    for (int l : f.Z->labels)
+        if (l != f.lh && l != f.lw && !op.C.has(l)) {
+            if (!f.F->has(l)) return false;
+            f.shared.push_back(l);
+        }
+    for (int l : f.F->labels)
+        if (l != f.lh && l != f.lw && !op.C.has(l) && !f.Z->has(l)) return false;
+    return true;
+}
+
+constexpr int64_t kDenseMax = 1 << 16;   // channels and rows
+
+// A convolution step with at least 16 rows and 8 channels: pack the kernel,
+// then dconv.  Against the general contraction it pays from about 16 M
+// multiplications on (X[16,128,28,28] stride 2 to 256 channels, bf16: 52 us
+// and its sum against 7 + 14 us); smaller steps are two launches either way.
+// One-tap steps need 128 channels (64 channels, 42 rows, 56x56 stride 2: 30
+// us either way).
+// `few`: steps of at most 16 rows, which the plane kernel (cred) walks rank by
+// rank in about one block a sample, some 0.06 us a (rank, row, tap); it keeps
+// the samples of about five blocks a CU in flight.  Measured cred / here:
+// X[16,200,28,28] to ranks 45 x 13, bf16, 463 / 20 us; one 14x14 sample of 32
+// planes x 128 channels to 8 rows, bf16, 452 / 18 us.
+bool try_dense_conv(const PairOp& op, bool few, ScratchAlloc& scratch, std::vector<Launch>& out) {
+    DenseForm f;
+    if (op.macs < (few ? 1u << 18 : 16u << 20) || op.C.dtype != op.L.dtype || !dense_form(op, f)) return false;
+    const TensorRef &Z = *f.Z, &F = *f.F, &C = op.C;
+    int64_t B, C_, M, x_sb, x_sc, y_sb, y_sm, n, sm, sc;
+    if (!merged(Z, f.only_z, B, x_sb) || !merged(C, f.only_z, n, y_sb) || !merged(F, f.only_f, M, sm) ||
+        !merged(C, f.only_f, n, y_sm) || !merged(Z, f.shared, C_, x_sc) || !merged(F, f.shared, n, sc))
+        return false;
+    if (M < (few ? 4 : 16) || (few && M > 16) || C_ < (f.h.J * f.w.J == 1 ? 128 : 8) || M > kDenseMax || C_ > kDenseMax || B > (1 << 24) || (f.h.bL != 1 && f.h.bL != -1) ||
+        (f.w.bL != 1 && f.w.bL != -1))
+        return false;
+    if (f.only_z.empty()) x_sb = C_ * x_sc;
+    // images outermost, so that one image's channels end before the next begins
+    if (x_sc < f.h.limL * f.w.limL || x_sb < C_ * x_sc) return false;
+    const bool bf = op.L.dtype == DT_BF16;
+    DConvDesc d;
+    std::memset(&d, 0, sizeof(d));
+    d.t.B = (int32_t)B;
+    d.t.H = (int32_t)f.h.limL;
+    d.t.W = (int32_t)f.w.limL;
+    d.t.OH = (int32_t)f.h.O;
+    d.t.OW = (int32_t)f.w.O;
+    d.t.KH = (int32_t)std::min<int64_t>(f.h.J, 99);
+    d.t.KW = (int32_t)std::min<int64_t>(f.w.J, 99);
+    if (f.h.gL < -64 || f.h.gL > 64 || f.w.gL < -64 || f.w.gL > 64) return false;
+    d.t.zh0 = (int32_t)f.h.gL;
+    d.t.zw0 = (int32_t)f.w.gL;
+    d.t.zhs = f.h.bL;
+    d.t.zws = f.w.bL;
+    d.t.sth = f.h.aL;
+    d.t.stw = f.w.aL;
+    d.C = (int32_t)C_;
+    d.M = (int32_t)M;
+    d.x_sb = x_sb;
+    d.x_sc = x_sc;
+    d.y_sb = y_sb;
+    d.y_sm = y_sm;
+    d.y_sh = C.stride_of(f.lh);
+    d.y_sw = C.stride_of(f.lw);
+    Launch lc;
+    if (!plan_dconv(d, bf, lc)) return false;
+    if (few) {
+        const double taps = (double)(f.h.J * f.w.J);
+        const double cred = std::max(1.0, (double)B / 1280) * (double)(C_ * M) * taps * 0.06;
+        const double steps = (double)(d.cfg == 2 ? (d.nch + 3) / 4 : d.nch) * taps * (bf ? 0.4 : 1.1);
+        if (15.0 + steps * (double)((d.blocks + 255) / 256) > cred) return false;
+    }
+    DPackDesc q;
+    std::memset(&q, 0, sizeof(q));
+    q.M = d.M;
+    q.C = d.C;
+    q.KH = d.t.KH;
+    q.KW = d.t.KW;
+    q.mt = (int32_t)cdiv(M, 32);
+    q.nch = d.nch;
+    q.sm = sm;
+    q.sc = sc;
+    q.sh = F.stride_of(f.lh);
+    q.sw = F.stride_of(f.lw);
+    const BufRef A = scratch.alloc((size_t)((int64_t)q.mt * q.nch * q.KH * q.KW * 2048));
+    Launch lp;
+    lp.kind = K_DPACK | dt_bits(op.L.dtype, op.L.dtype, op.L.dtype);
+    lp.a = F.buf;
+    lp.c = A;
+    lp.grid[0] = (uint32_t)cdiv((int64_t)q.mt * q.nch * 128, 256);
+    lp.block[0] = 256;
+    set_desc(lp, q);
+    lp.kname = std::string("dpack<") + tname(op.L.dtype) + ">";
+    lc.a = Z.buf;
+    lc.b = A;
+    lc.c = C.buf;
+    out.push_back(lp);
+    out.push_back(lc);
+    return true;
+}
+
+// The kernel's gradient of such a step: dwgrad and the ordered sum.
+// `least`: channels (before the plane-convolution kernels are tried, 16).
+bool try_dense_wgrad(const PairOp& op, int least, ScratchAlloc& scratch, std::vector<Launch>& out) {
+    DenseForm f;
+    if (op.macs < (16u << 20) || !dense_form(op, f)) return false;
+    const TensorRef &Z = *f.Z, &F = *f.F, &C = op.C;   // F: the output gradient, positions j
+    if (f.h.aL != 1 || f.w.aL != 1 || f.h.bL < 1 || f.w.bL < 1 || F.stride_of(f.lw) != 1 ||
+        F.stride_of(f.lh) != f.w.J || f.h.O > 5 || f.w.O > 5)
+        return false;
+    int64_t T, S, B, g_sc, g_sb, x_sc, x_sb, st, ss, n;
+    if (!merged(F, f.only_f, T, g_sc) || !merged(C, f.only_f, n, st) || !merged(Z, f.only_z, S, x_sc) ||
+        !merged(C, f.only_z, n, ss) || !merged(Z, f.shared, B, x_sb) || !merged(F, f.shared, n, g_sb))
+        return false;
+    if (T < 16 || S < least || T > kDenseMax || S > kDenseMax || B > (1 << 24)) return false;
+    if (f.shared.empty()) {
+        x_sb = S * x_sc;
+        g_sb = T * g_sc;
+    }
+    if (x_sc < f.h.limL * f.w.limL || x_sb < S * x_sc || g_sc < f.h.J * f.w.J || g_sb < T * g_sc) return false;
+    if (f.h.gL < -64 || f.h.gL > 64 || f.w.gL < -64 || f.w.gL > 64) return false;
+    const bool bf = op.L.dtype == DT_BF16;
+    // fp32 5x5 gradients stay on the plane kernel's MFMA tiles where it
+    // applies (64 x 64 channels, X[100,14,14]: 76 us against 122)
+    if (least == 16 && !bf && f.h.O * f.w.O > 12) return false;
+    DWgradDesc d;
+    std::memset(&d, 0, sizeof(d));
+    d.t.B = (int32_t)B;
+    d.t.H = (int32_t)f.h.limL;
+    d.t.W = (int32_t)f.w.limL;
+    d.t.OH = (int32_t)f.h.J;
+    d.t.OW = (int32_t)f.w.J;
+    d.t.KH = (int32_t)f.h.O;
+    d.t.KW = (int32_t)f.w.O;
+    d.t.zh0 = (int32_t)f.h.gL;
+    d.t.zw0 = (int32_t)f.w.gL;
+    d.t.zhs = d.t.zws = 1;
+    d.t.sth = f.h.bL;
+    d.t.stw = f.w.bL;
+    d.T = (int32_t)T;
+    d.S = (int32_t)S;
+    d.x_sb = x_sb;
+    d.x_sc = x_sc;
+    d.g_sb = g_sb;
+    d.g_sc = g_sc;
+    Launch lw;
+    if (!plan_dwgrad(d, bf, 16 << 20, lw)) return false;
+    const BufRef P = scratch.alloc((size_t)((int64_t)d.nsplit * d.t.KH * d.t.KW * T * S) * 4);
+    lw.a = F.buf;
+    lw.b = Z.buf;
+    lw.d = P;
+    out.push_back(lw);
+    DWredDesc r;
+    std::memset(&r, 0, sizeof(r));
+    r.T = d.T;
+    r.S = d.S;
+    r.KH = d.t.KH;
+    r.KW = d.t.KW;
+    r.nsplit = d.nsplit;
+    r.st = st;
+    r.ss = ss;
+    r.sh = C.stride_of(f.lh);
+    r.sw = C.stride_of(f.lw);
+    Launch lr;
+    lr.kind = K_DWRED | dt_bits(DT_F32, DT_F32, C.dtype);
+    lr.d = P;
+    lr.c = C.buf;
+    lr.grid[0] = (uint32_t)cdiv(T * S * d.t.KH * d.t.KW, 256);
+    lr.block[0] = 256;
+    set_desc(lr, r);
+    lr.kname = std::string("dwred<") + tname(C.dtype) + ">";
+    out.push_back(lr);
+    return true;
+}
+
+}  // namespace
+
+// Lowering of one pairwise op (declared in plan.h).
 std::vector<Launch> lower_op(const ce_expr& e, const PairOp& op, unsigned flags,
                              ScratchAlloc& scratch) {
     (void)e;
@@ -1487,9 +1715,22 @@ std::vector<Launch> lower_op(const ce_expr& e, const PairOp& op, unsigned flags,
             return out;
         }
     }
+    // 5x5 steps over more than 32 channels: the conv-contraction kernel's
+    // filter slice fills the LDS (64 x 64 channels, X[100,14,14], bf16: 218 us
+    // against 30 dense; 16 channels to 32 rows: 10 against 19 us)
+    auto wide5 = [](const PairOp& o) {
+        DenseForm f;
+        int64_t n, st;
+        return o.convs.size() == 2 && o.convs[0].J * o.convs[1].J == 25 && dense_form(o, f) &&
+               merged(*f.Z, f.shared, n, st) && n > 32;
+    };
     bool fast = !(flags & CE_FLAG_GENERIC_ONLY) && !op.generic_only && !circular &&
                 (try_gemm(op, out) || try_wgrad(op, scratch, out) || try_dw(op, scratch, out) ||
-                 try_cred(op, scratch, out) || try_cconv(op, out) || try_thinw(op, scratch, out) ||
+                 try_dense_conv(op, true, scratch, out) || try_dense_wgrad(op, 16, scratch, out) ||
+                 try_cred(op, scratch, out) || (wide5(op) && try_dense_conv(op, false, scratch, out)) ||
+                 try_cconv(op, out) ||
+                 try_dense_conv(op, false, scratch, out) || try_dense_wgrad(op, 8, scratch, out) ||
+                 try_thinw(op, scratch, out) ||
                  try_tc(op, scratch, out, (flags & CE_FLAG_WIDE_OFFSETS) != 0));
     if (!fast) {
         out.clear();
@@ -1511,10 +1752,11 @@ std::vector<Launch> lower_op(const ce_expr& e, const PairOp& op, unsigned flags,
     }
     // the main launch of a split op carries the op's bytes and flops
     if (out.size() == 2) {
-        out[0].alg_bytes = bytes;
-        out[0].alg_flops = 2.0 * (double)op.macs;
-        out[1].alg_bytes = 0;
-        out[1].alg_flops = 0;
+        const int main = (out[0].kind & 0xff) == K_DPACK ? 1 : 0;
+        out[main].alg_bytes = bytes;
+        out[main].alg_flops = 2.0 * (double)op.macs;
+        out[1 - main].alg_bytes = 0;
+        out[1 - main].alg_flops = 0;
     }
     return out;
 }
@@ -1552,29 +1794,39 @@ bool dense_tile(DTile& t, int64_t px) {
 
 bool plan_dconv(DConvDesc& d, bool bf16, Launch& ln) {
     const int64_t es = bf16 ? 2 : 4, CK = bf16 ? 32 : 16;
-    // rows, pixels and MFMAs a wavefront issues per tap of a chunk half
-    static const struct { int rows, px; double cost; } cfgs[] = {{64, 256, 4 / 0.7}, {64, 128, 2 / 0.55}, {64, 64, 1 / 0.4}};
-    if (d.t.KH != d.t.KW || (d.t.KH != 3 && d.t.KH != 5)) return false;
+    const int KH = d.t.KH, KW = d.t.KW;
+    const bool big = (KH == 3 && KW == 3) || (KH == 5 && KW == 5), small = KH >= 1 && KH <= 2 && KW >= 1 && KW <= 2;
+    if (!big && !small) return false;
+    // rows and pixels of a block; its time a (chunk, tap) relative to the
+    // others: MFMAs a wavefront over the share of the matrix rate it reaches
+    static const struct { int rows, px; double bf, f; } cfgs[] = {
+        {64, 256, 4 / 0.7, 4 / 0.85}, {64, 128, 2 / 0.55, 2 / 0.8}, {64, 64, 1 / 0.4, 1 / 0.75}};
     d.nch = (int32_t)((d.C + CK - 1) / CK);
     double best = 0;
     DConvDesc r = d;
     bool found = false;
     for (int c = 0; c < 3; c++) {
-        DConvDesc e = d;
-        if (!dense_tile(e.t, cfgs[c].px)) continue;
-        // cfg 2: a buffer pair a wavefront, and room for the four sums
-        const int64_t lds = c == 2 ? std::max<int64_t>(65536, 8 * (int64_t)e.t.slots * 80) : 2 * (int64_t)e.t.slots * 80;
-        if (lds > kLdsMax || es * e.t.NI * d.x_sb >= (1ll << 31)) continue;
-        e.cfg = c;
-        e.mblk = (d.M + cfgs[c].rows - 1) / cfgs[c].rows;
-        e.lds_bytes = (uint32_t)lds;
-        e.blocks = (int64_t)e.mblk * e.t.npt;
-        if (e.blocks > 0x7fffffff) continue;
-        const double cost = (double)((e.blocks + 255) / 256) * cfgs[c].cost;
-        if (found && cost >= best) continue;
-        best = cost;
-        r = e;
-        found = true;
+        if (c == 1 && !big) continue;
+        // strided tiles stage more slots than pixels: fewer pixels where the LDS ends
+        for (int64_t px = cfgs[c].px; px >= cfgs[c].px / 4; px -= cfgs[c].px / 4) {
+            DConvDesc e = d;
+            if (!dense_tile(e.t, px)) continue;
+            // cfg 2: a buffer pair a wavefront, and room for the four sums
+            const int64_t lds = c == 2 ? std::max<int64_t>(65536, 8 * (int64_t)e.t.slots * 80) : 2 * (int64_t)e.t.slots * 80;
+            if (lds > kLdsMax || es * e.t.NI * d.x_sb >= (1ll << 31)) continue;
+            e.cfg = c;
+            e.mblk = (d.M + cfgs[c].rows - 1) / cfgs[c].rows;
+            e.lds_bytes = (uint32_t)lds;
+            e.blocks = (int64_t)e.mblk * e.t.npt;
+            if (e.blocks > 0x7fffffff) break;
+            const double cost = (double)((e.blocks + 255) / 256) * (bf16 ? cfgs[c].bf : cfgs[c].f);
+            if (!found || cost < best) {
+                best = cost;
+                r = e;
+                found = true;
+            }
+            break;
+        }
     }
     if (!found) return false;
     d = r;
@@ -1583,21 +1835,22 @@ bool plan_dconv(DConvDesc& d, bool bf16, Launch& ln) {
     ln.grid[0] = (uint32_t)d.blocks;
     ln.block[0] = 256;
     ln.lds = d.lds_bytes;
-    ln.desc.resize(sizeof(d));
-    std::memcpy(ln.desc.data(), &d, sizeof(d));
+    set_desc(ln, d);
     static const char* tp[] = {"1, 1, 4, 2, 2", "1, 2, 2, 1, 2", "4, 1, 1, 2, 2"};
-    ln.kname = std::string("dconv<") + (bf16 ? "unsigned short, " : "float, ") + std::to_string(d.t.KH) + ", " + tp[d.cfg] + ">";
+    ln.kname = std::string("dconv<") + (bf16 ? "unsigned short, " : "float, ") + std::to_string(KH) + ", " +
+               std::to_string(KW) + ", " + tp[d.cfg] + ">";
     const double px = (double)d.t.B * d.t.OH * d.t.OW;
-    ln.alg_flops = 2.0 * px * d.M * d.C * d.t.KH * d.t.KW;
-    ln.alg_bytes = (double)es * (px * d.M + (double)d.t.B * d.t.H * d.t.W * d.C + (double)d.M * d.C * d.t.KH * d.t.KW);
+    ln.alg_flops = 2.0 * px * d.M * d.C * KH * KW;
+    ln.alg_bytes = (double)es * (px * d.M + (double)d.t.B * d.t.H * d.t.W * d.C + (double)d.M * d.C * KH * KW);
     return true;
 }
 
 bool plan_dwgrad(DWgradDesc& d, bool bf16, int64_t max_partial_bytes, Launch& ln) {
     const int64_t es = bf16 ? 2 : 4, KT = (int64_t)d.t.KH * d.t.KW;
-    const int cfg = KT <= 10 ? 0 : KT <= 28 ? 1 : -1;
+    const int cfg = KT == 1 ? 2 : KT <= (bf16 ? 10 : 12) ? 0 : KT <= 28 ? 1 : -1;
     if (cfg < 0) return false;
-    const int64_t NS = cfg == 0 ? 2 : 1, pg = 64 * es + 16, px = 32 * NS * es + (NS == 1 && bf16 ? 32 : 16);
+    const int64_t NS = cfg == 2 ? 4 : cfg == 0 && bf16 ? 2 : 1, pg = 64 * es + 16;
+    const int64_t px = 32 * NS * es + (NS == 1 && bf16 ? 32 : 16);
     const int64_t zspan = (int64_t)(d.t.KH - 1);
     bool found = false;
     for (int64_t want : {256, 192, 128, 96, 64, 32}) {
@@ -1608,7 +1861,8 @@ bool plan_dwgrad(DWgradDesc& d, bool bf16, int64_t max_partial_bytes, Launch& ln
         d.lds_bytes = (uint32_t)(d.o_tab + 4 * d.PP);
         // at most four staging units a thread (512 threads) of either operand
         const int64_t gu = 64 * es / 16 * d.PP, xu = 32 * NS * es / 16 * d.t.slots;
-        if (gu > 2048 || xu > 2048 || d.lds_bytes > kLdsMax || es * d.t.NI * std::max(d.x_sb, d.g_sb) >= (1ll << 31)) continue;
+        if (gu > 2048 || xu > 2048 || d.lds_bytes > kLdsMax ||
+            es * d.t.NI * std::max(d.x_sb, d.g_sb) >= (1ll << 31)) continue;
         found = true;
         break;
     }
@@ -1627,9 +1881,9 @@ bool plan_dwgrad(DWgradDesc& d, bool bf16, int64_t max_partial_bytes, Launch& ln
     ln.grid[0] = (uint32_t)d.blocks;
     ln.block[0] = 512;
     ln.lds = d.lds_bytes;
-    ln.desc.resize(sizeof(d));
-    std::memcpy(ln.desc.data(), &d, sizeof(d));
-    ln.kname = std::string("dwgrad<") + (bf16 ? "unsigned short, " : "float, ") + (cfg == 0 ? "2, 2, 5>" : "1, 4, 7>");
+    set_desc(ln, d);
+    static const char* tp[2][3] = {{"1, 4, 3>", "1, 4, 7>", "4, 1, 1>"}, {"2, 2, 5>", "1, 4, 7>", "4, 1, 1>"}};
+    ln.kname = std::string("dwgrad<") + (bf16 ? "unsigned short, " : "float, ") + tp[bf16][cfg];
     const double pxs = (double)d.t.B * d.t.OH * d.t.OW;
     ln.alg_flops = 2.0 * pxs * d.T * d.S * KT;
     ln.alg_bytes = es * (pxs * d.T + (double)d.t.B * d.t.H * d.t.W * d.S) + (double)d.nsplit * one;

@@ -1504,12 +1504,51 @@ bool run_dconv(const Launch& ln, Ctx& c) {
     return true;
 }
 
+bool run_dpack(const Launch& ln, Ctx& c) {
+    DPackDesc d = desc_of<DPackDesc>(ln);
+    const int bf = (ln.kind >> kBitIn) & 1, EPU = bf ? 8 : 4, KT = d.KH * d.KW;
+    bool ok = true, o1, o2;
+    Buf F = resolve(ln.a, c, 0, o1), A = resolve(ln.c, c, 0, o2);
+    REQ(o1 && o2 && d.mt == (d.M + 31) / 32 && d.nch == (d.C + 4 * EPU - 1) / (4 * EPU) && ln.block[0] == 256 &&
+        (int64_t)ln.grid[0] * 256 >= (int64_t)d.mt * d.nch * 128, "pack layout");
+    for (int64_t u = 0; u < (int64_t)d.mt * d.nch * 128; u++) {
+        const int l = (int)(u & 63), k = (int)(u >> 6) & 1;
+        const int64_t mc = u >> 7;
+        const int row = (int)(mc / d.nch) * 32 + (l & 31), c0 = (int)(mc % d.nch) * 4 * EPU + (2 * k + (l >> 5)) * EPU;
+        for (int j = 0; j < KT; j++)
+            for (int e = 0; e < EPU; e++) {
+                const bool live = row < d.M && c0 + e < d.C;
+                const float v = live ? ld(F, bf, row * d.sm + (c0 + e) * d.sc + (j / d.KW) * d.sh + (j % d.KW) * d.sw, ok) : 0.f;
+                st(A, bf, ((mc * KT + j) * 128 + (u & 127)) * EPU + e, v, ok);
+            }
+    }
+    REQ(ok, "out-of-bounds (pack)");
+    return true;
+}
+
+bool run_dwred(const Launch& ln, Ctx& c) {
+    DWredDesc d = desc_of<DWredDesc>(ln);
+    const int tC = (ln.kind >> kBitOut) & 1, KT = d.KH * d.KW;
+    bool ok = true, o1, o2;
+    Buf P = resolve(ln.d, c, 0, o1), C = resolve(ln.c, c, 0, o2);
+    const int64_t n = (int64_t)d.T * d.S * KT;
+    REQ(o1 && o2 && ln.block[0] == 256 && (int64_t)ln.grid[0] * 256 >= n, "kernel gradient sum");
+    for (int64_t u = 0; u < n; u++) {
+        double acc = 0;
+        for (int sp = 0; sp < d.nsplit; sp++) acc += ld(P, 0, sp * n + u, ok);
+        const int64_t s2 = u % d.S, t = u / d.S % d.T, j = u / d.S / d.T;
+        st(C, tC, t * d.st + s2 * d.ss + (j / d.KW) * d.sh + (j % d.KW) * d.sw, (float)acc, ok);
+    }
+    REQ(ok, "out-of-bounds (kernel gradient sum)");
+    return true;
+}
+
 bool run_dwgrad(const Launch& ln, Ctx& c) {
     DWgradDesc d = desc_of<DWgradDesc>(ln);
     const DTile& t = d.t;
-    const int bf = (ln.kind >> kBitIn) & 1, es = bf ? 2 : 4, KT = t.KH * t.KW, NS = d.cfg == 0 ? 2 : 1;
+    const int bf = (ln.kind >> kBitIn) & 1, es = bf ? 2 : 4, KT = t.KH * t.KW, NS = d.cfg == 2 ? 4 : d.cfg == 0 && bf ? 2 : 1;
     const int64_t pg = 64 * es + 16, px = 32 * NS * es + (NS == 1 && bf ? 32 : 16);
-    REQ((d.cfg == 0 ? KT <= 10 : d.cfg == 1 && KT <= 28) && check_tile(t, d.PP, ln, c) && d.PP % 16 == 0 && d.PP <= 512 &&
+    REQ((d.cfg == 2 ? KT == 1 : d.cfg == 0 ? KT <= (bf ? 10 : 12) : d.cfg == 1 && KT <= 28) && check_tile(t, d.PP, ln, c) && d.PP % 16 == 0 && d.PP <= 512 &&
         64 * es / 16 * d.PP <= 2048 && 32 * NS * es / 16 * t.slots <= 2048 && d.o_x == d.PP * pg &&
         d.o_tab == d.o_x + (t.slots + (t.KH - 1) * t.WP + t.KW) * px && d.lds_bytes == d.o_tab + 4 * d.PP &&
         ln.lds == d.lds_bytes && ln.lds <= 160 * 1024 && d.ntb == (d.T + 63) / 64 && d.nsb == (d.S + 32 * NS - 1) / (32 * NS) &&
@@ -2014,6 +2053,8 @@ int emul_run(const char* spec, int n, const int* ranks, const int64_t* const* di
                     : v == K_FILL ? run_fill(ln, c)
                     : v == K_DCONV ? run_dconv(ln, c)
                     : v == K_DWGRAD ? run_dwgrad(ln, c)
+                    : v == K_DPACK ? run_dpack(ln, c)
+                    : v == K_DWRED ? run_dwred(ln, c)
                     : v == K_RCP_MERGE ? run_rcp_merge(ln, c)
                     : v == K_RCP_FGRAD ? run_rcp_fgrad(ln, c)
                     : v == K_RCP_DFWD ? run_rcp_dfwd(ln, c)

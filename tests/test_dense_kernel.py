@@ -78,3 +78,48 @@ def test_gpu(name):
     # the same values again, and a gradient alone as among the others
     part = plan.backward(xs, d, needs=[False, True, False, False, True])
     assert torch.equal(part[1], g[1]) and torch.equal(part[4], g[4]) and part[0] is None
+
+
+# (string, shapes, strides): a convolution step against one four-label kernel,
+# off the tiles: partial channel chunks and rows, 5x5, strided planes with odd
+# sizes, one tap, few rows on few samples
+STEPS = {
+    "k3": ("bshw,tshw->bthw|hw", [(5, 50, 13, 27), (70, 50, 3, 3)], None),
+    "k5": ("bshw,tshw->bthw|hw", [(3, 33, 19, 14), (34, 33, 5, 5)], None),
+    "k3_s2": ("bshw,tshw->bthw|hw", [(40, 48, 29, 28), (80, 48, 3, 3)], {"h": 2, "w": 2}),
+    "k1_s2": ("bshw,tshw->bthw|hw", [(16, 130, 21, 28), (140, 130, 1, 1)], {"h": 2, "w": 2}),
+    "k5_s1x3": ("bshw,tshw->bthw|hw", [(20, 40, 20, 17), (48, 40, 5, 5)], {"w": 3}),
+    "few_rows": ("bshw,tshw->bthw|hw", [(2, 90, 28, 28), (13, 90, 3, 3)], None),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name", sorted(STEPS))
+def test_gpu_step(name, dtype):
+    """One step: bf16 results are rounded once (2^-9 relative at most), fp32
+    ones hold the fp32 bar with two-level sums."""
+    import torch
+    import paper_2401_03384_amd as P
+    spec, shapes, strides = STEPS[name]
+    rng = np.random.default_rng(3)
+    e = O.bind(O.parse(spec), shapes, strides=strides or {})
+    rnd = (lambda a: W.round_to_bf16(a)) if dtype == "bf16" else (lambda a: a.astype(np.float32))
+    ins = [rnd(rng.standard_normal(s)).astype(np.float64) for s in shapes]
+    plan = P.Plan(spec, shapes, dtype, strides=strides)
+    dy = rnd(rng.standard_normal(plan.out_shape)).astype(np.float64)
+    text = plan.describe()
+    assert "dwgrad<" in text or name == "few_rows" or (name, dtype) in (("k1_s2", "f32"), ("k5", "f32")), text
+    if dtype == "f32" or strides or name == "few_rows":
+        assert "dconv<" in text, text
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dev = lambda a: torch.from_numpy(a.astype(np.float32)).to(tdt).cuda()  # noqa: E731
+    xs, d = [dev(a) for a in ins], dev(dy)
+    y = plan.forward(xs)
+    g = plan.backward(xs, d)
+    host = lambda t: t.double().cpu().numpy()  # noqa: E731
+    tol = 2.0 ** -9 if dtype == "bf16" else 1e-6
+    assert _rel(host(y), O.eval_dense(e, ins)) <= tol
+    ref = O.grads_dense(e, ins, dy)
+    assert _rel(host(g[0]), ref[0]) <= tol
+    assert _rel(host(g[1]), ref[1]) <= 1e-6 * 2   # fp32 sums of exact (bf16) or fp32 products
