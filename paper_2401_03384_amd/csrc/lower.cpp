@@ -1263,7 +1263,7 @@ bool try_tc(const PairOp& op, ScratchAlloc& scratch, std::vector<Launch>& out, b
 // The step C[g][k][n] = sum_m A[g][m][n] F[k][m] (fp32); gl = its "grad lhs"
 // op (dC x rhs -> d lhs), gr = its "grad rhs" op (lhs x dC -> d rhs).
 bool try_gpair_ops(const PairOp& gl, const PairOp& gr, ScratchAlloc& scratch, std::vector<Launch>& out,
-                   int& fside) {
+                   int& fside, bool lean) {
     if (!gl.has_r || !gr.has_r || !gl.convs.empty() || !gr.convs.empty()) return false;
     const TensorRef& Gt = gl.L;   // the output gradient
     for (int side = 0; side < 2; side++) {
@@ -1396,7 +1396,7 @@ bool try_gpair_ops(const PairOp& gl, const PairOp& gr, ScratchAlloc& scratch, st
         // against 10 + 11 + 6 us; one 56x56 sample: 115 against 24 us).
         const double serial = (double)cdiv(d.blocks, 256) * d.gper * d.ntiles * d.nkc * (d.blocks < 256 ? 2.4 : 1.6);
         const double moved = 2 * tensor_bytes(Gt) + 2 * tensor_bytes(At);
-        if (serial > (d.nkc == 1 ? 25.0 : 20.0 + 9.0 * d.nkc) + moved / 2.5e6 + 4.0 * (double)gl.macs / 40e6) continue;
+        if (!lean && serial > (d.nkc == 1 ? 25.0 : 20.0 + 9.0 * d.nkc) + moved / 2.5e6 + 4.0 * (double)gl.macs / 40e6) continue;
         const BufRef part = scratch.alloc((size_t)(d.blocks * fnumel * 4));
         Launch ln;
         ln.kind = K_GPAIR | dt_bits(DT_F32, DT_F32, DT_F32);
@@ -1440,7 +1440,7 @@ std::vector<Launch> lower_grad_pair(const PairOp& gl, const PairOp& gr, unsigned
     std::vector<Launch> out;
     if ((flags & (CE_FLAG_GENERIC_ONLY | CE_FLAG_NO_FUSION)) || gl.generic_only || gr.generic_only) return out;
     int fside = 0;
-    if (!try_gpair_ops(gl, gr, scratch, out, fside)) {
+    if (!try_gpair_ops(gl, gr, scratch, out, fside, (flags & kFlagLean) != 0)) {
         out.clear();
         return out;
     }
@@ -1724,12 +1724,13 @@ std::vector<Launch> lower_op(const ce_expr& e, const PairOp& op, unsigned flags,
         return o.convs.size() == 2 && o.convs[0].J * o.convs[1].J == 25 && dense_form(o, f) &&
                merged(*f.Z, f.shared, n, st) && n > 32;
     };
+    const bool dense = !(flags & kFlagLean);
     bool fast = !(flags & CE_FLAG_GENERIC_ONLY) && !op.generic_only && !circular &&
                 (try_gemm(op, out) || try_wgrad(op, scratch, out) || try_dw(op, scratch, out) ||
-                 try_dense_conv(op, true, scratch, out) || try_dense_wgrad(op, 16, scratch, out) ||
-                 try_cred(op, scratch, out) || (wide5(op) && try_dense_conv(op, false, scratch, out)) ||
+                 (dense && (try_dense_conv(op, true, scratch, out) || try_dense_wgrad(op, 16, scratch, out))) ||
+                 try_cred(op, scratch, out) || (dense && wide5(op) && try_dense_conv(op, false, scratch, out)) ||
                  try_cconv(op, out) ||
-                 try_dense_conv(op, false, scratch, out) || try_dense_wgrad(op, 8, scratch, out) ||
+                 (dense && (try_dense_conv(op, false, scratch, out) || try_dense_wgrad(op, 8, scratch, out))) ||
                  try_thinw(op, scratch, out) ||
                  try_tc(op, scratch, out, (flags & CE_FLAG_WIDE_OFFSETS) != 0));
     if (!fast) {

@@ -650,8 +650,11 @@ uint64_t pair_cost(const ce_expr& e, uint32_t A, uint32_t B, ce_cost_mode mode) 
     return c;
 }
 
-ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned flags,
-                   bool use_path, const int* pairs, int n_pairs, const PlanLimits& lim) {
+namespace {
+
+// lean: the backward without the kernels of lower.cpp that kFlagLean names.
+ce_plan* build_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned flags, bool use_path,
+                    const int* pairs, int n_pairs, const PlanLimits& lim, bool lean) {
     if (!e.bound) fail(CE_ERR_ARG, "expression is not bound");
     for (int l = 0; l < e.num_labels(); l++)
         if (e.stride_of(l) > 1 && e.feature_of(l) < 0)
@@ -934,6 +937,7 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
         patch(p->fwd, items);
 
         // ---------------- backward ----------------
+        const unsigned bflags = lean ? flags | kFlagLean : flags;
         // timeline: recompute step t at time t (t < m-1); backward of step s at
         // time (m-1) + (m-1-s).
         std::vector<WsItem> bitems;
@@ -1016,7 +1020,7 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
             op.C = bgrad(0);
             op.need = 1u;
             op.what = "unary bwd";
-            for (auto& l : lower_op(E, op, flags, bs)) p->bwd.push_back(l);
+            for (auto& l : lower_op(E, op, bflags, bs)) p->bwd.push_back(l);
         }
         // intermediates the forward left in the workspace are read there (a
         // fused backward recomputes on chip and reads none)
@@ -1045,7 +1049,7 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
             op.macs = st.macs;
             op.what = "step " + std::to_string(s) + " recompute";
             bs.t = s;
-            for (auto& l : lower_op(E, op, flags, bs)) p->bwd.push_back(l);
+            for (auto& l : lower_op(E, op, bflags, bs)) p->bwd.push_back(l);
         }
         for (int s = m - 1; !fused_bwd && s >= 0; s--) {
             const Step& st = p->steps[s];
@@ -1070,15 +1074,15 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
                       tensor_str(E, gr.R) + "->" + tensor_str(E, gr.C);
             // a channel-mixing step: both gradients from one read of dC
             std::vector<Launch> pair;
-            if (gl.convs.empty() && gr.convs.empty()) pair = lower_grad_pair(gl, gr, flags, bs);
+            if (gl.convs.empty() && gr.convs.empty()) pair = lower_grad_pair(gl, gr, bflags, bs);
             if (!pair.empty()) {
                 for (auto& l : pair) p->bwd.push_back(l);
                 continue;
             }
             for (const PairOp& q : bld.phase_split(st, 1, gl))
-                for (auto& l : lower_op(E, q, flags, bs)) p->bwd.push_back(l);
+                for (auto& l : lower_op(E, q, bflags, bs)) p->bwd.push_back(l);
             for (const PairOp& q : bld.phase_split(st, 2, gr))
-                for (auto& l : lower_op(E, q, flags, bs)) p->bwd.push_back(l);
+                for (auto& l : lower_op(E, q, bflags, bs)) p->bwd.push_back(l);
         }
         drop_unused(bitems, p->bwd);
         p->ws_bwd = pack(bitems);
@@ -1091,6 +1095,23 @@ ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned
             bitems.insert(bitems.end(), kept.begin(), kept.end());
         }
         patch(p->bwd, bitems);
+    }
+    return p.release();
+}
+
+}  // namespace
+
+// The dense convolution kernels hold a packed kernel and partial sums of its
+// gradient (1024 x 1024 channels, 3x3, fp32: 75 MB of backward workspace
+// against 57 MB without them).  A backward that fits the allocation-free entry
+// point only without them does without them.
+ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned flags,
+                   bool use_path, const int* pairs, int n_pairs, const PlanLimits& lim) {
+    std::unique_ptr<ce_plan> p(build_plan(e, mode, dtype, flags, use_path, pairs, n_pairs, lim, false));
+    const size_t most = CE_NOALLOC_WORKSPACE_BYTES;
+    if (p->ws_bwd > most && p->save_mask == 0 && !(flags & CE_FLAG_GENERIC_ONLY)) {
+        std::unique_ptr<ce_plan> q(build_plan(e, mode, dtype, flags, use_path, pairs, n_pairs, lim, true));
+        if (q->ws_bwd <= most) return q.release();
     }
     return p.release();
 }

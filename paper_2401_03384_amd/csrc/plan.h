@@ -117,6 +117,10 @@ struct PlanLimits {
     uint64_t save_budget = 0;                // bytes of intermediates kept for the backward
 };
 
+// Lowering without the kernels that trade workspace for speed (the dense
+// convolution steps, separate launches where the gradient pair fits).
+constexpr unsigned kFlagLean = 0x80000000u;
+
 // Build a plan: the optimal order when use_path is false, else the order
 // given by `pairs` (opt_einsum path format, n_pairs = n_in - 1).
 ce_plan* make_plan(const ce_expr& e, ce_cost_mode mode, ce_dtype dtype, unsigned flags,

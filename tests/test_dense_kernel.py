@@ -123,3 +123,21 @@ def test_gpu_step(name, dtype):
     ref = O.grads_dense(e, ins, dy)
     assert _rel(host(g[0]), ref[0]) <= tol
     assert _rel(host(g[1]), ref[1]) <= 1e-6 * 2   # fp32 sums of exact (bf16) or fp32 products
+
+
+@pytest.mark.parametrize("channels,dtype,strides,dense", [
+    (512, "f32", None, True),                      # 18.9 MB with the dense kernels
+    (1024, "f32", None, False),                    # 75.5 MB with them, 56.6 without
+    (1408, "bf16", {"h": 2, "w": 2}, False),       # 107 MB with them, 9.0 without
+    (2048, "f32", {"h": 2, "w": 2}, False),        # 302 MB with them, 18.9 without
+    (1408, "f32", None, True),                     # over the limit either way
+])
+def test_allocation_free_backward_kept(channels, dtype, strides, dense):
+    """A backward that fits the allocation-free entry point without the dense
+    convolution kernels is not taken past its limit by them."""
+    import paper_2401_03384_amd as P
+    plan = P.Plan("bshw,tshw->bthw|hw", [(2, channels, 8, 8), (channels, channels, 3, 3)], dtype, strides=strides)
+    bwd = [line for line in plan.describe().splitlines() if line.startswith("  bwd ")]
+    assert any("dwgrad<" in line or "dconv<" in line for line in bwd) == dense, bwd
+    if not (dense and channels > 1024):
+        assert P.ce_plan_workspace_size(plan.handle, 1) <= 64 << 20
